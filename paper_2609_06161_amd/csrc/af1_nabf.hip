@@ -22,6 +22,7 @@
 // bit.
 #include <math.h>
 #include <mutex>
+#include <type_traits>
 
 #include <rocblas/rocblas.h>
 #include <rocsolver/rocsolver.h>
@@ -44,41 +45,147 @@ constexpr int kChunk = 64;       // rows per partial-sum tile
 // Device kernels
 // ---------------------------------------------------------------------------
 
-// part[chunk][j] = sum over tokens of the chunk of X[t][j]^2 (bf16 input).
-__global__ __launch_bounds__(256) void colsq_kernel(const uint16_t *__restrict__ X, int T, int n,
-                                                    float *__restrict__ part) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= n) return;
-  const int t0 = blockIdx.y * kChunk;
-  const int t1 = min(T, t0 + kChunk);
-  float s = 0.f;
-  for (int t = t0; t < t1; ++t) {
-    const float v = bf16_to_f32(X[(size_t)t * n + j]);
-    s += v * v;
+// Sum of v over the 64 lanes, in every lane (fixed order): four DPP steps
+// within rows of 16, then the four rows.  Register moves only; the shuffles
+// of wave_sum go through LDS, six dependent round trips.
+template <int kCtrl>
+__device__ __forceinline__ float dpp_f32(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float wave_sum_dpp(float v) {
+  v += dpp_f32<0xB1>(v);
+  v += dpp_f32<0x4E>(v);
+  v += dpp_f32<0x124>(v);
+  v += dpp_f32<0x128>(v);
+  const int b = __float_as_int(v);
+  return (__int_as_float(__builtin_amdgcn_readlane(b, 0)) +
+          __int_as_float(__builtin_amdgcn_readlane(b, 16))) +
+         (__int_as_float(__builtin_amdgcn_readlane(b, 32)) +
+          __int_as_float(__builtin_amdgcn_readlane(b, 48)));
+}
+
+// Sums of squares per 64-token tile of X (T x n) and G (T x m), bf16, in one
+// launch: part[tile][j].  A workgroup takes 256 columns of one matrix: 32
+// threads of 8 columns (16-byte loads) by 8 groups of 8 tokens, all of a
+// thread's loads in flight at once (rows past T load row T - 1 and add
+// nothing), the groups added in order through LDS.  Bound by memory latency:
+// one 2-byte load a thread and token, each waited for in turn, took 17.4 us
+// per matrix at 2048 x 4096 (16.8 MB); both together now take 7.1.
+constexpr int kColsqGroups = 8;
+__global__ __launch_bounds__(256) void colsq_kernel(const uint16_t *__restrict__ X, int n,
+                                                    float *__restrict__ px, int xblocks,
+                                                    const uint16_t *__restrict__ G, int m,
+                                                    float *__restrict__ pg, int T) {
+  __shared__ float red[kColsqGroups][256 + 8];
+  const bool first = (int)blockIdx.x < xblocks;  // uniform
+  const uint16_t *src = first ? X : G;
+  const int cols = first ? n : m;
+  const int c0 = 256 * ((int)blockIdx.x - (first ? 0 : xblocks));
+  const int cx = threadIdx.x & 31, tg = threadIdx.x >> 5;
+  const int c = c0 + 8 * cx;
+  const int cl = c < cols ? c : 0;
+  const int t0 = (int)blockIdx.y * kChunk + tg * (kChunk / kColsqGroups);
+  uint4 v[kChunk / kColsqGroups];
+#pragma unroll
+  for (int q = 0; q < kChunk / kColsqGroups; ++q)
+    v[q] = *reinterpret_cast<const uint4 *>(src + (size_t)min(t0 + q, T - 1) * cols + cl);
+  float s[8] = {};
+#pragma unroll
+  for (int q = 0; q < kChunk / kColsqGroups; ++q) {
+    const uint32_t d[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+    const bool use = t0 + q < T;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float a = __uint_as_float(d[e] << 16), b = __uint_as_float(d[e] & 0xffff0000u);
+      s[2 * e] += use ? a * a : 0.f;
+      s[2 * e + 1] += use ? b * b : 0.f;
+    }
   }
-  part[(size_t)blockIdx.y * n + j] = s;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) red[tg][8 * cx + e] = s[e];
+  __syncthreads();
+  const int j = c0 + (int)threadIdx.x;
+  if (j < cols) {
+    float t = 0.f;
+#pragma unroll
+    for (int k = 0; k < kColsqGroups; ++k) t += red[k][threadIdx.x];
+    (first ? px : pg)[(size_t)blockIdx.y * cols + j] = t;
+  }
 }
 
-// out[j] = sqrt(sum over chunks of part[chunk][j] / T), chunks added in order.
-__global__ __launch_bounds__(256) void rms_finish_kernel(const float *__restrict__ part, int chunks,
-                                                         int n, int T, float *__restrict__ out) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= n) return;
-  float s = 0.f;
-  for (int c = 0; c < chunks; ++c) s += part[(size_t)c * n + j];
-  out[j] = sqrtf(s / (float)T);
+// Column sums of partial rows: out[j] = sum over the chunks of
+// part[chunk][j], for up to two matrices in one launch (blocks below `split`
+// take the first).  A workgroup takes 64 columns: 16 float4 columns by 16
+// chunk groups (group g adds chunks g, g + 16, ..., eight loads in flight),
+// the groups added in order through LDS.  kRms: out = sqrt(sum / T), the
+// surrogate's column RMS.  One thread a column,
+// each chunk waited for in turn, took 16 us at 64 chunks x 2016 columns;
+// 512 chunks now take 4.3.
+constexpr int kSumCols = 64;
+struct ColSum {
+  const float *part;
+  float *out;
+  int chunks, cols;
+};
+template <bool kRms>
+__global__ __launch_bounds__(256) void colsum_kernel(ColSum a, ColSum b, int split, int T) {
+  __shared__ float4 red[16][17];
+  const bool first = (int)blockIdx.x < split;  // uniform
+  const ColSum p = first ? a : b;
+  const int c4 = threadIdx.x & 15, g = threadIdx.x >> 4;
+  const int j = kSumCols * ((int)blockIdx.x - (first ? 0 : split)) + 4 * c4;
+  const int jl = j < p.cols ? j : 0;
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int k0 = g; k0 < p.chunks; k0 += 16 * 8) {
+    float4 v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      v[q] = *reinterpret_cast<const float4 *>(
+          p.part + (size_t)min(k0 + 16 * q, p.chunks - 1) * p.cols + jl);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const bool use = k0 + 16 * q < p.chunks;
+      s.x += use ? v[q].x : 0.f;
+      s.y += use ? v[q].y : 0.f;
+      s.z += use ? v[q].z : 0.f;
+      s.w += use ? v[q].w : 0.f;
+    }
+  }
+  red[g][c4] = s;
+  __syncthreads();
+  if (g == 0 && j < p.cols) {
+    float4 t = red[0][c4];
+#pragma unroll
+    for (int k = 1; k < 16; ++k) {
+      const float4 r = red[k][c4];
+      t.x += r.x;
+      t.y += r.y;
+      t.z += r.z;
+      t.w += r.w;
+    }
+    if constexpr (kRms) {
+      const float f = (float)T;
+      t = make_float4(sqrtf(t.x / f), sqrtf(t.y / f), sqrtf(t.z / f), sqrtf(t.w / f));
+    }
+    *reinterpret_cast<float4 *>(p.out + j) = t;
+  }
 }
 
-// Wp[u][j] = o[u] * W[u][j] * i[j].
+// Wp[u][j] = o[u] * W[u][j] * i[j], a float4 a thread (cols % 32 == 0): 20.2
+// us at 4096^2 (134 MB, 6.6 TB/s) against 28.8 with one float a thread.
 __global__ __launch_bounds__(256) void surrogate_scale_kernel(const float *__restrict__ W, int64_t m,
                                                               int n, const float *__restrict__ o,
                                                               const float *__restrict__ iv,
                                                               float *__restrict__ Wp) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
+  const int j = 4 * ((int)blockIdx.x * 256 + (int)threadIdx.x);
   if (j >= n) return;
-  const float ij = iv[j];
-  for (int64_t u = blockIdx.y; u < m; u += gridDim.y)
-    Wp[u * n + j] = o[u] * W[u * n + j] * ij;
+  const float4 ij = *reinterpret_cast<const float4 *>(iv + j);
+  for (int64_t u = blockIdx.y; u < m; u += gridDim.y) {
+    const float4 v = *reinterpret_cast<const float4 *>(W + u * n + j);
+    const float ou = o[u];
+    *reinterpret_cast<float4 *>(Wp + u * n + j) =
+        make_float4(ou * v.x * ij.x, ou * v.y * ij.y, ou * v.z * ij.z, ou * v.w * ij.w);
+  }
 }
 
 __global__ __launch_bounds__(256) void fill_kernel(float *__restrict__ v, int n, float val) {
@@ -102,6 +209,158 @@ __global__ __launch_bounds__(256) void abs_rowdot_kernel(const float *__restrict
   }
   s = wave_sum(s);
   if (lane == 0) u[i] = s;
+}
+
+// One power-iteration pass of the SVID, Z read once.  A workgroup takes a
+// block of rows: for each row u = |Z_i| v (a reduction over the workgroup),
+// then w += |Z_i| u from the same registers, and the block's w goes to
+// part[block].  colsum_kernel adds the blocks.  A thread holds kQ float4 of
+// every row (columns 4 (tid + threads q) ..), so kQ * threads * 4 >= cols;
+// kR rows are reduced together (one barrier), the next kR rows loading
+// meanwhile.
+//
+// v is the normalised w of the pass before, recomputed by every workgroup
+// (each thread needs its own columns of it anyway): v = w / ||w||, kept from
+// the pass before (`right`) when w is zero; w == nullptr: the constant v0.
+// Workgroup 0 stores v to `right`; where the others read `right` (w zero),
+// it stores the values that are there.
+//
+// kLast: the final left = |Z| v instead of w, and the signs of Z packed as
+// af1_pack does (eight lanes' sign nibbles make a word).
+//
+// Bound by the read of Z, which the last-level cache holds between passes at
+// calibration sizes.  Separate row and column passes with a finishing and a
+// normalising launch read Z twice: 43.7 us a pass at 4096 x 2016 (33 MB);
+// this pass takes 6.9 us there and the column sums 4.3 (kernel trace).
+template <int kQ, int kR, int kThreads, bool kLast>
+__global__ __launch_bounds__(kThreads) void svid_pass_kernel(
+    const float *__restrict__ Z, int rows, int cols, int rows_wg, const float *__restrict__ w,
+    float v0, float *right, float *__restrict__ part, float *__restrict__ left,
+    uint32_t *__restrict__ bits) {
+  constexpr int kWaves = kThreads / 64;
+  __shared__ float red[2][kR][kWaves];
+  const int tid = threadIdx.x, wave = tid >> 6;
+  const int nf = cols / 4;  // float4 of a row
+  bool live[kQ];
+  int col[kQ];
+#pragma unroll
+  for (int q = 0; q < kQ; ++q) {
+    live[q] = tid + kThreads * q < nf;
+    col[q] = live[q] ? 4 * (tid + kThreads * q) : 0;  // loads stay inside the arrays
+  }
+  const int i0 = (int)blockIdx.x * rows_wg;
+  const int i1 = min(rows, i0 + rows_wg);
+  auto load = [&](float4 (&z)[kR][kQ], int i) {
+#pragma unroll
+    for (int r = 0; r < kR; ++r)
+#pragma unroll
+      for (int q = 0; q < kQ; ++q)
+        z[r][q] = *reinterpret_cast<const float4 *>(Z + (size_t)min(i + r, i1 - 1) * cols + col[q]);
+  };
+  float4 za[kR][kQ], zb[kR][kQ];
+  load(za, i0);
+
+  // v
+  float4 v[kQ];
+  if (w) {
+    float s = 0.f;
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      v[q] = *reinterpret_cast<const float4 *>(w + col[q]);
+      s += live[q] ? v[q].x * v[q].x + v[q].y * v[q].y + v[q].z * v[q].z + v[q].w * v[q].w : 0.f;
+    }
+    s = wave_sum_dpp(s);
+    if ((tid & 63) == 0) red[1][0][wave] = s;
+    __syncthreads();
+    s = red[1][0][0];
+#pragma unroll
+    for (int k = 1; k < kWaves; ++k) s += red[1][0][k];
+    const float norm = sqrtf(s);
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      if (s > 0.f)
+        v[q] = make_float4(v[q].x / norm, v[q].y / norm, v[q].z / norm, v[q].w / norm);
+      else
+        v[q] = *reinterpret_cast<const float4 *>(right + col[q]);
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) v[q] = make_float4(v0, v0, v0, v0);
+  }
+#pragma unroll
+  for (int q = 0; q < kQ; ++q) {
+    if (blockIdx.x == 0 && live[q]) *reinterpret_cast<float4 *>(right + col[q]) = v[q];
+    if (!live[q]) v[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+
+  float4 acc[kQ];
+#pragma unroll
+  for (int q = 0; q < kQ; ++q) acc[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+  // rows i .. i + kR - 1 (in z); the red buffers alternate, so one barrier a
+  // batch is enough
+  auto batch = [&](const float4 (&z)[kR][kQ], int i, int buf) {
+    float u[kR];
+#pragma unroll
+    for (int r = 0; r < kR; ++r) {
+      float s = 0.f;
+#pragma unroll
+      for (int q = 0; q < kQ; ++q)
+        s += live[q] ? fabsf(z[r][q].x) * v[q].x + fabsf(z[r][q].y) * v[q].y +
+                           fabsf(z[r][q].z) * v[q].z + fabsf(z[r][q].w) * v[q].w
+                     : 0.f;
+      u[r] = wave_sum_dpp(s);
+    }
+    if ((tid & 63) == 0) {
+#pragma unroll
+      for (int r = 0; r < kR; ++r) red[buf][r][wave] = u[r];
+    }
+    // LDS only: the next batch's loads stay in flight
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+    for (int r = 0; r < kR; ++r) {
+      float t = red[buf][r][0];
+#pragma unroll
+      for (int k = 1; k < kWaves; ++k) t += red[buf][r][k];
+      const bool use = i + r < i1;  // uniform
+      if constexpr (kLast) {
+        if (use && tid == 0) left[i + r] = t;
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) {
+          const float4 f = z[r][q];
+          uint32_t n = (__float_as_uint(f.x) >> 31) | (__float_as_uint(f.y) >> 31) << 1 |
+                       (__float_as_uint(f.z) >> 31) << 2 | (__float_as_uint(f.w) >> 31) << 3;
+          n <<= 4 * (tid & 7);
+          n |= __shfl_xor(n, 1, 8);
+          n |= __shfl_xor(n, 2, 8);
+          n |= __shfl_xor(n, 4, 8);
+          if (use && live[q] && (tid & 7) == 0) bits[(size_t)(i + r) * (cols / 32) + col[q] / 32] = n;
+        }
+      } else {
+        const float uu = use ? t : 0.f;
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) {
+          // a row past the block adds nothing (its data is another row's)
+          acc[q].x += use ? fabsf(z[r][q].x) * uu : 0.f;
+          acc[q].y += use ? fabsf(z[r][q].y) * uu : 0.f;
+          acc[q].z += use ? fabsf(z[r][q].z) * uu : 0.f;
+          acc[q].w += use ? fabsf(z[r][q].w) * uu : 0.f;
+        }
+      }
+    }
+  };
+  for (int i = i0; i < i1; i += 2 * kR) {
+    load(zb, min(i + kR, i1 - 1));
+    batch(za, i, 0);
+    if (i + kR >= i1) break;
+    load(za, min(i + 2 * kR, i1 - 1));
+    batch(zb, i + kR, 1);
+  }
+  if constexpr (!kLast) {
+#pragma unroll
+    for (int q = 0; q < kQ; ++q)
+      if (live[q])
+        *reinterpret_cast<float4 *>(part + (size_t)blockIdx.x * cols + col[q]) = acc[q];
+  }
 }
 
 // part[chunk][j] = sum over the chunk's rows i of |Z[i][j]| u[i].
@@ -492,8 +751,71 @@ size_t svid_layout(int64_t rows, int64_t cols, uint8_t *base, Ws *w) {
 
 // ---- building blocks (arguments already validated) ------------------------
 
+// Rows a workgroup of svid_pass_kernel takes: few enough for two workgroups
+// per compute unit, at least kSvidMinRows (below it the partial sums cost
+// more than the read of Z: every workgroup writes one row of them), and no
+// fewer than the scratch of part_floats holds (64 rows always fit).
+constexpr int kSvidMinRows = 4;
+int compute_units() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      cus <= 0)
+    return 256;
+  return cus;
+}
+int svid_rows_wg(int64_t rows, int64_t cols, size_t part_floats) {
+  int rw = kSvidMinRows;
+  while (rw < kChunk && ((rows + rw - 1) / rw > 2 * (int64_t)compute_units() ||
+                         (size_t)((rows + rw - 1) / rw) * cols > part_floats))
+    rw *= 2;
+  return rw;
+}
+
+template <int kQ, int kR, int kThreads>
+af1_status svid_fused(const float *Z, int64_t rows, int64_t cols, int iters, uint32_t *bits,
+                      float *left, float *right, float *part, size_t part_floats, float *w,
+                      hipStream_t s) {
+  const int rw = svid_rows_wg(rows, cols, part_floats);
+  const unsigned blocks = (unsigned)((rows + rw - 1) / rw);
+  const unsigned cb = (unsigned)((cols + kSumCols - 1) / kSumCols);
+  const float v0 = 1.0f / sqrtf((float)cols);
+  for (int it = 0; it < iters; ++it) {
+    svid_pass_kernel<kQ, kR, kThreads, false><<<blocks, kThreads, 0, s>>>(
+        Z, (int)rows, (int)cols, rw, it == 0 ? nullptr : w, v0, right, part, nullptr, nullptr);
+    CHECK_LAUNCH();
+    const ColSum c{part, w, (int)blocks, (int)cols};
+    colsum_kernel<false><<<cb, 256, 0, s>>>(c, c, (int)cb, 1);
+    CHECK_LAUNCH();
+  }
+  svid_pass_kernel<kQ, kR, kThreads, true><<<blocks, kThreads, 0, s>>>(
+      Z, (int)rows, (int)cols, rw, iters == 0 ? nullptr : w, v0, right, nullptr, left, bits);
+  CHECK_LAUNCH();
+  return AF1_OK;
+}
+
+// part_floats: the floats that w.svid_part may use (at least
+// chunks_of(rows) * cols).
 af1_status run_svid(const float *Z, int64_t rows, int64_t cols, int iters, uint32_t *bits,
-                    float *left, float *right, const Ws &w, hipStream_t s) {
+                    float *left, float *right, const Ws &w, size_t part_floats, hipStream_t s) {
+  // Rows of up to 16384 columns live in the registers of one workgroup;
+  // more float4 a thread first (fewer waves to reduce over), then more
+  // threads.
+  auto fused = [&](auto Q, auto R, auto N) {
+    return svid_fused<decltype(Q)::value, decltype(R)::value, decltype(N)::value>(
+        Z, rows, cols, iters, bits, left, right, w.svid_part, part_floats, w.svid_w, s);
+  };
+  using std::integral_constant;
+  if (cols <= 1024)
+    return fused(integral_constant<int, 1>{}, integral_constant<int, 4>{}, integral_constant<int, 256>{});
+  if (cols <= 2048)
+    return fused(integral_constant<int, 2>{}, integral_constant<int, 4>{}, integral_constant<int, 256>{});
+  if (cols <= 4096)
+    return fused(integral_constant<int, 4>{}, integral_constant<int, 2>{}, integral_constant<int, 256>{});
+  if (cols <= 8192)
+    return fused(integral_constant<int, 4>{}, integral_constant<int, 2>{}, integral_constant<int, 512>{});
+  if (cols <= 16384)
+    return fused(integral_constant<int, 4>{}, integral_constant<int, 2>{}, integral_constant<int, 1024>{});
   const unsigned cb = blocks_for(cols);
   const int64_t chunks = chunks_of(rows);
   fill_kernel<<<cb, 256, 0, s>>>(right, (int)cols, 1.0f / sqrtf((float)cols));
@@ -674,7 +996,11 @@ af1_status run_iteration(rocblas_handle h, const float *Wp, const af1_nabf_state
   if (st != AF1_OK) return st;
   add_kernel<<<grid_cap(m * r), 256, 0, s>>>(w.hat_a, S->UA, w.z, m * r);
   CHECK_LAUNCH();
-  st = run_svid(w.z, m, r, iters, S->A_bits, S->a, S->m1, w, s);
+  // the SVID's partial sums go where the fit's product will (free until then)
+  Ws wsv = w;
+  wsv.svid_part = w.ep;
+  const size_t ep_floats = (size_t)(m > n ? m : n) * r;
+  st = run_svid(w.z, m, r, iters, S->A_bits, S->a, S->m1, wsv, ep_floats, s);
   if (st != AF1_OK) return st;
   st = projector_from_eig(h, r, eta, w.p, nullptr, w, s);   // null space of B B^T
   if (st != AF1_OK) return st;
@@ -692,7 +1018,7 @@ af1_status run_iteration(rocblas_handle h, const float *Wp, const af1_nabf_state
   if (st != AF1_OK) return st;
   add_kernel<<<grid_cap(r * n), 256, 0, s>>>(w.hat_b, S->UB, w.z, r * n);
   CHECK_LAUNCH();
-  st = run_svid(w.z, r, n, iters, S->B_bits, S->m2, S->b, w, s);
+  st = run_svid(w.z, r, n, iters, S->B_bits, S->m2, S->b, wsv, ep_floats, s);
   if (st != AF1_OK) return st;
   st = projector_from_eig(h, r, eta, w.p, nullptr, w, s);   // null space of A^T A
   if (st != AF1_OK) return st;
@@ -758,15 +1084,16 @@ af1_status af1_nabf_surrogate(const float *W, int64_t m, int64_t n, const uint16
   hipStream_t s = as_stream(stream);
   const int64_t chunks = chunks_of(T);
   float *px = w.rms_part, *pg = w.rms_part + chunks * n;
-  colsq_kernel<<<dim3(blocks_for(n), (unsigned)chunks), 256, 0, s>>>(X, (int)T, (int)n, px);
+  const unsigned xb = blocks_for(n);
+  colsq_kernel<<<dim3(xb + blocks_for(m), (unsigned)chunks), 256, 0, s>>>(
+      X, (int)n, px, (int)xb, G, (int)m, pg, (int)T);
   CHECK_LAUNCH();
-  colsq_kernel<<<dim3(blocks_for(m), (unsigned)chunks), 256, 0, s>>>(G, (int)T, (int)m, pg);
+  const ColSum cx{px, i_vec, (int)chunks, (int)n}, cg{pg, o_vec, (int)chunks, (int)m};
+  const unsigned sx = (unsigned)((n + kSumCols - 1) / kSumCols);
+  const unsigned sg = (unsigned)((m + kSumCols - 1) / kSumCols);
+  colsum_kernel<true><<<sx + sg, 256, 0, s>>>(cx, cg, (int)sx, (int)T);
   CHECK_LAUNCH();
-  rms_finish_kernel<<<blocks_for(n), 256, 0, s>>>(px, (int)chunks, (int)n, (int)T, i_vec);
-  CHECK_LAUNCH();
-  rms_finish_kernel<<<blocks_for(m), 256, 0, s>>>(pg, (int)chunks, (int)m, (int)T, o_vec);
-  CHECK_LAUNCH();
-  surrogate_scale_kernel<<<dim3(blocks_for(n), rows_grid(m)), 256, 0, s>>>(W, m, (int)n, o_vec,
+  surrogate_scale_kernel<<<dim3(blocks_for((n + 3) / 4), rows_grid(m)), 256, 0, s>>>(W, m, (int)n, o_vec,
                                                                            i_vec, Wp);
   CHECK_LAUNCH();
   return AF1_OK;
@@ -782,7 +1109,15 @@ af1_status af1_svid(const float *Z, int64_t rows, int64_t cols, int32_t iters, u
   Ws w;
   const size_t need = svid_layout(rows, cols, static_cast<uint8_t *>(ws), &w);
   if (!ws || ws_bytes < need) return AF1_ERR_WORKSPACE;
-  return run_svid(Z, rows, cols, iters, bits, left, right, w, as_stream(stream));
+  // what the workspace holds past the required layout serves the partial sums
+  // too: they move behind the other arrays, where the rest is theirs
+  size_t part_floats = (size_t)chunks_of(rows) * cols;
+  const size_t spare = (ws_bytes - need) / 4;
+  if (spare > part_floats) {
+    w.svid_part = reinterpret_cast<float *>(static_cast<uint8_t *>(ws) + need);
+    part_floats = spare;
+  }
+  return run_svid(Z, rows, cols, iters, bits, left, right, w, part_floats, as_stream(stream));
 }
 
 af1_status af1_nullspace_projector(const float *C, int64_t r, float eta, float *P, int32_t *k_out,
