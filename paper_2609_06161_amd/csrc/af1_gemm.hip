@@ -52,6 +52,8 @@
 // Few tokens.  When the tile grid leaves compute units idle, a forward
 // contraction splits its K steps over grid z and a reduction launch adds
 // the fp32 partials in split order (see plan_contraction).
+#include <math.h>
+
 #include <utility>
 
 #include "af1_device.h"
@@ -142,6 +144,19 @@ __device__ __forceinline__ void copy4(i32x4 r, uint8_t *dst, int voff) {
   asm volatile("buffer_load_dword %0, %1, 0 offen lds" ::"v"(voff), "s"(r), "{m0}"(m) : "memory");
 }
 
+// The same with a scalar offset added to every lane's (range checks include
+// it).
+__device__ __forceinline__ void copy16s(i32x4 r, uint8_t *dst, int voff, int soff) {
+  const uint32_t m = (uint32_t)(size_t)(lds_void *)dst;
+  asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(voff), "s"(r), "s"(soff), "{m0}"(m)
+               : "memory");
+}
+__device__ __forceinline__ void copy4s(i32x4 r, uint8_t *dst, int voff, int soff) {
+  const uint32_t m = (uint32_t)(size_t)(lds_void *)dst;
+  asm volatile("buffer_load_dword %0, %1, %2 offen lds" ::"v"(voff), "s"(r), "s"(soff), "{m0}"(m)
+               : "memory");
+}
+
 __device__ __forceinline__ void wait_copies() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Wait until at most N vector memory operations of this wave are in flight
@@ -150,6 +165,18 @@ template <int N>
 __device__ __forceinline__ void wait_copies_but() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+
+// Wait until at most N copies are in flight and this wave's LDS reads are
+// done, then meet the workgroup.  Builtins rather than inline assembly, so
+// that the compiler knows that no LDS read is pending.
+template <int N>
+__device__ __forceinline__ void step_barrier() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));  // lgkmcnt 0
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
 template <typename F, int... I>
@@ -227,9 +254,11 @@ __host__ __device__ constexpr int slot_exp(int e) {
   return e == 0 ? 14 : e == 1 ? 13 : e == 2 ? 11 : 7;
 }
 // G1's per-tile row sums of the intermediate: RS[t][b] = sum of a_k over the
-// 256 columns of tile b (the second product adds them up into R2_t), rows
-// of rs_ld(r) floats.
-__host__ __device__ constexpr int rs_ld(int64_t r) { return (int)((((r + 255) / 256) + 3) & ~3); }
+// rs_w columns of tile b (the second product adds them up into R2_t), rows
+// of rs_ld(r, rs_w) floats.
+__host__ __device__ constexpr int rs_ld(int64_t r, int rs_w) {
+  return (int)((((r + rs_w - 1) / rs_w) + 3) & ~3);
+}
 
 // Exponent c_t of the intermediate's scale: 2^-c_t L_t smax' < 1, with
 // smax' = max|s_mid| (1 when every s_mid is zero).  0 for an all-zero row.
@@ -642,7 +671,7 @@ __global__ __launch_bounds__(kThreads, 2) void bingemm_kernel(
     const uint16_t *__restrict__ rowscale, uint16_t *__restrict__ C, uint16_t *__restrict__ V,
     const uint16_t *__restrict__ S, float *__restrict__ F, const float *__restrict__ gscale,
     int split_steps, float *__restrict__ P, int mix_full, int mix_splits, int mix_nN,
-    float *__restrict__ tinfo, float *__restrict__ RS) {
+    float *__restrict__ tinfo, float *__restrict__ RS, int rs_nb, int rs_ldv) {
   constexpr bool kPairOut = kMode == kMid || kMode == kMidSave || kMode == kBwdMid;
   constexpr bool kBwd = kMode == kBwdMid || kMode == kBwdIn;
   constexpr bool kFirst = kMode == kMid || kMode == kMidSave;
@@ -755,7 +784,7 @@ __global__ __launch_bounds__(kThreads, 2) void bingemm_kernel(
     if constexpr (kFirst) {
       tab_r = tinfo_r1(tinfo, T)[t];
     } else {
-      const int nb = (K + 255) / 256, ld = rs_ld(K);
+      const int nb = rs_nb, ld = rs_ldv;
       const float4 *rr = reinterpret_cast<const float4 *>(RS + (size_t)t * ld);
       for (int b0 = 0; b0 < nb; b0 += 16) {
         float4 v[4];
@@ -1091,7 +1120,7 @@ __global__ __launch_bounds__(kThreads, 2) void bingemm_kernel(
           a = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, d[e]), half2v{f, f}, a, false);
         }
         const float rsum = half_wave_sum(a);
-        if (chunk == 0 && t0 + row < T) RS[(size_t)(t0 + row) * rs_ld(N) + n0 / BN] = rsum;
+        if (chunk == 0 && t0 + row < T) RS[(size_t)(t0 + row) * rs_ld(N, BN) + n0 / BN] = rsum;
       }
     }
   };
@@ -1633,7 +1662,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
   const float a = finish8<kMode>(lo, hi, in, pc, t, N, C, V, F, live);
   if constexpr (kPairOut) {
     const float rsum = half_wave_sum(a);
-    if ((u & 31) == 0) RS[(size_t)t * rs_ld(N) + p / 256] = rsum;
+    if ((u & 31) == 0) RS[(size_t)t * rs_ld(N, 256) + p / 256] = rsum;
   }
 }
 
@@ -1696,8 +1725,60 @@ __global__ __launch_bounds__(256) void mixed_reduce_kernel(const float *__restri
   const float asum = finish8<kMode>(lo, hi, in, n0 + pl, t, N, C, V, F, live);
   if constexpr (kPairOut) {
     const float rsum = half_wave_sum(asum);
-    if ((unit & 31) == 0) RS[(size_t)t * rs_ld(N) + L % nN] = rsum;
+    if ((unit & 31) == 0) RS[(size_t)t * rs_ld(N, BN) + L % nN] = rsum;
   }
+}
+
+// The backward modes' outputs for 8 consecutive output positions of one
+// token from their fp32 accumulator sums (lo, hi as in finish8): the C
+// values, packed, and g = gradient * S for the token sums, element e being
+// output position p + e.  gs: the token's group scales; sq: its 8 S values.
+template <int kMode>
+__device__ __forceinline__ uint4 bwd_finish8(const float4 &lo, const float4 &hi, const Fin8In &in,
+                                             const float2 &gs, const uint4 &sq, float (&g)[8]) {
+  constexpr bool kPairOut = kMode == kBwdMid;
+  const float fg = kMode == kBwdMid ? gs.x : gs.x / gs.y;
+  // kBwdMid: S is the saved intermediate at the forward's per-token scale
+  // (saved_v_shift from the prefetched record)
+  const int vsh = kMode == kBwdMid ? mid_exp(in.ti.x, in.smax) - smax_exp(in.smax) -
+                                         __float_as_int(in.ti.y)
+                                   : 0;
+  // row scales of columns cl .. cl+3 (rsv[0..3]) and ch .. ch+3 (rsv[4..7])
+  const uint32_t rw[4] = {in.rlo.x, in.rlo.y, in.rhi.x, in.rhi.y};
+  float rsv[8];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    rsv[2 * k] = f16_lo(rw[k]);
+    rsv[2 * k + 1] = f16_hi(rw[k]);
+  }
+  const float l4[4] = {lo.x, lo.y, lo.z, lo.w}, h4[4] = {hi.x, hi.y, hi.z, hi.w};
+  float acc[8], rse[8];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    acc[kPairOut ? 2 * k : k] = l4[k];
+    acc[kPairOut ? 2 * k + 1 : 4 + k] = h4[k];
+    rse[kPairOut ? 2 * k : k] = rsv[k];              // column cl + k
+    rse[kPairOut ? 2 * k + 1 : 4 + k] = rsv[4 + k];  // column ch + k
+  }
+  // S is stored like C: fp16 in pair order (kBwdMid), bf16 natural (kBwdIn)
+  const uint32_t sw[4] = {sq.x, sq.y, sq.z, sq.w};
+  uint32_t c[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    float o[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int e = 2 * k + h;
+      const uint32_t sbits = h ? sw[k] >> 16 : sw[k] & 0xffffu;
+      const float sval = kMode == kBwdMid ? f16_to_f32((uint16_t)sbits) : bf16_to_f32(sbits);
+      g[e] = kMode == kBwdMid ? ldexpf(acc[e] * fg * sval, vsh) : acc[e] * fg * sval;
+      const float rs = rse[e];
+      o[h] = kMode == kBwdMid ? acc[e] * rs * gs.y : acc[e] * fg * rs;
+    }
+    c[k] = kMode == kBwdMid ? (uint32_t)f32_to_f16(o[0]) | ((uint32_t)f32_to_f16(o[1]) << 16)
+                            : (uint32_t)f32_to_bf16(o[0]) | ((uint32_t)f32_to_bf16(o[1]) << 16);
+  }
+  return make_uint4(c[0], c[1], c[2], c[3]);
 }
 
 // The reduction of a split-K backward contraction.  A workgroup takes 64
@@ -1736,49 +1817,8 @@ __global__ __launch_bounds__(256) void splitk_bwd_reduce_kernel(
     const Fin8In in = finish8_load<kMode == kBwdMid, 0>(cl, ch, t, T, rowscale, tinfo);
     float4 lo, hi;
     sum_partials<kBatch>(P + (size_t)t * N, (size_t)T * N, S, cl, ch, lo, hi);
-    const float fg = kMode == kBwdMid ? gs.x : gs.x / gs.y;
-    // kBwdMid: S is the saved intermediate at the forward's per-token scale
-    // (saved_v_shift from the prefetched record)
-    const int vsh = kMode == kBwdMid ? mid_exp(in.ti.x, in.smax) - smax_exp(in.smax) -
-                                           __float_as_int(in.ti.y)
-                                     : 0;
-    // row scales of columns cl .. cl+3 (rsv[0..3]) and ch .. ch+3 (rsv[4..7])
-    const uint32_t rw[4] = {in.rlo.x, in.rlo.y, in.rhi.x, in.rhi.y};
-    float rsv[8];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      rsv[2 * k] = f16_lo(rw[k]);
-      rsv[2 * k + 1] = f16_hi(rw[k]);
-    }
-    const float l4[4] = {lo.x, lo.y, lo.z, lo.w}, h4[4] = {hi.x, hi.y, hi.z, hi.w};
-    float acc[8], rse[8];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      acc[kPairOut ? 2 * k : k] = l4[k];
-      acc[kPairOut ? 2 * k + 1 : 4 + k] = h4[k];
-      rse[kPairOut ? 2 * k : k] = rsv[k];          // column cl + k
-      rse[kPairOut ? 2 * k + 1 : 4 + k] = rsv[4 + k];  // column ch + k
-    }
-    // S is stored like C: fp16 in pair order (kBwdMid), bf16 natural (kBwdIn)
-    const uint32_t sw[4] = {sq.x, sq.y, sq.z, sq.w};
-    uint32_t c[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      float o[2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int e = 2 * k + h;
-        const uint32_t sbits = h ? sw[k] >> 16 : sw[k] & 0xffffu;
-        const float sval = kMode == kBwdMid ? f16_to_f32((uint16_t)sbits) : bf16_to_f32(sbits);
-        g[e] = kMode == kBwdMid ? ldexpf(acc[e] * fg * sval, vsh) : acc[e] * fg * sval;
-        const float rs = rse[e];
-        o[h] = kMode == kBwdMid ? acc[e] * rs * gs.y : acc[e] * fg * rs;
-      }
-      c[k] = kMode == kBwdMid
-                 ? (uint32_t)f32_to_f16(o[0]) | ((uint32_t)f32_to_f16(o[1]) << 16)
-                 : (uint32_t)f32_to_bf16(o[0]) | ((uint32_t)f32_to_bf16(o[1]) << 16);
-    }
-    if (C) *reinterpret_cast<uint4 *>(C + (size_t)t * N + p) = make_uint4(c[0], c[1], c[2], c[3]);
+    const uint4 c = bwd_finish8<kMode>(lo, hi, in, gs, sq, g);
+    if (C) *reinterpret_cast<uint4 *>(C + (size_t)t * N + p) = c;
   }
   // token sums: red[token][position in block], then one thread per position
   // adds the 64 tokens in order and writes the column's sum
@@ -1798,6 +1838,392 @@ __global__ __launch_bounds__(256) void splitk_bwd_reduce_kernel(
   }
 }
 
+// ---------------------------------------------------------------------------
+// The contraction for grids of small tiles (few tokens, or a product too
+// small for the 128 x 256 tiles to fill the device): the same operands,
+// products and outputs as bingemm_kernel, with
+//  - tiles of kTM tokens x kTN weight rows, small enough that the grid fills
+//    the device without cutting K into partial sums: 64 x 128, 32 x 128 or
+//    32 x 64 (plan_contraction chooses; 128 x 128 and 64 x 64 tiles, and four
+//    waves of twice the rows, measured no better);
+//  - eight waves: kWT x kWR over the tile's tokens and rows, and kWK over the
+//    MFMA steps of a K step (the waves' partial tiles are added in LDS);
+//  - a pipeline of kS K steps of 128 kSub columns in LDS, the operands of the
+//    next step read into registers during this one's products.  A workgroup
+//    has a compute unit almost to itself here, so what bounds it is the
+//    latency of its own chain: with two steps (one in flight) a K step took a
+//    memory round trip, about 1.5 us against 0.2 us of MFMAs.
+// Per 256 columns with one workgroup a unit: 1790 cycles (64 x 128), 1000 (32
+// x 128) and 650 (32 x 64), of which the MFMAs are 1024, 512 and 256 and the
+// copies (64 bytes a cycle) 560, 320 and 290; the rest is the waves' own
+// instruction stream, which runs in step.
+// Copies past the row end, the last token or the workgroup's K range are out
+// of range and write zeros, so every wave issues the same count a step and
+// one s_waitcnt leaves exactly the later steps' copies in flight.
+//
+// With grid z > 1 a workgroup writes the fp32 partial of its K steps to P
+// (natural order), for the split-K reductions.  Otherwise the epilogue is
+// the reductions': a thread finishes 8 positions of a token at a time.
+// grid x: the tiles (nN a row of tiles); rs_nb, rs_ld: entries of RS a token,
+// and their row length.
+// ---------------------------------------------------------------------------
+template <int kTM_, int kTN_, int kWT_, int kWR_, int kWK_, int kSub_, int kS_>
+struct TokTile {
+  static constexpr int kTM = kTM_, kTN = kTN_, kWT = kWT_, kWR = kWR_, kWK = kWK_, kSub = kSub_,
+                       kS = kS_;
+  static constexpr int kWaves = kWT * kWR * kWK, kThreads = 64 * kWaves;
+  static constexpr int kTB = kTM / 32 / kWT, kRB = kTN / 32 / kWR;  // blocks a wave
+  static constexpr int kStep = 128 * kSub;                          // columns of a K step
+  static constexpr int kASub = kTM * 256, kWSub = kTN * 16;         // bytes of 128 columns
+  static constexpr int kStage = kSub * (kASub + kWSub);
+  static constexpr int kACopies = kSub * kASub / 1024 / kWaves;     // per wave and step
+  static constexpr int kWCopies = kSub * kWSub / 256 / kWaves;
+  static constexpr int kCopies = kACopies + kWCopies;
+  static constexpr int kRedLd = kTN + 4;  // floats of a staged fp32 token row
+  static constexpr int kRed = kWK * kTM * kRedLd * 4;
+  static constexpr int kTab = kS * kStage > kRed ? kS * kStage : kRed;
+  // per token: tinfo pair, row sum; row scales
+  static constexpr int kBytes = kTab + kTM * 8 + kTM * 4 + kTN * 2;
+  static_assert(kTB * kWT * 32 == kTM && kRB * kWR * 32 == kTN, "blocks cover the tile");
+  static_assert(kACopies * kWaves * 1024 == kSub * kASub && kWCopies * kWaves * 256 == kSub * kWSub,
+                "the same copies in every wave");
+  static_assert((kS - 1) * kCopies < 64, "s_waitcnt range");
+  static_assert(8 % kWK == 0 && 8 / kWK >= 2, "whole sign words a wave");
+  static_assert(kBytes <= 160 * 1024, "LDS");
+};
+
+template <int kMode, typename TT>
+__global__ __launch_bounds__(TT::kThreads) void tokgemm_kernel(
+    const uint16_t *__restrict__ A, const uint32_t *__restrict__ W, int T, int K, int N, int nN,
+    int total, int split_steps, const uint16_t *__restrict__ rowscale, float *__restrict__ tinfo,
+    float *__restrict__ RS, const float *__restrict__ gscale, int rs_nb, int rs_ld,
+    uint16_t *__restrict__ C, uint16_t *__restrict__ V, const uint16_t *__restrict__ S,
+    float *__restrict__ F, float *__restrict__ P) {
+  constexpr bool kPairOut = kMode == kMid || kMode == kMidSave || kMode == kBwdMid;
+  constexpr bool kBwd = kMode == kBwdMid || kMode == kBwdIn;
+  constexpr bool kFirst = kMode == kMid || kMode == kMidSave;
+  constexpr int kTM = TT::kTM, kTN = TT::kTN, kTB = TT::kTB, kRB = TT::kRB, kS = TT::kS;
+  constexpr int kNks = 8 / TT::kWK;  // MFMA steps of a wave in 128 columns
+  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wk = wave % TT::kWK, wr = wave / TT::kWK % TT::kWR, wt = wave / TT::kWK / TT::kWR;
+
+  const int kw = K / 32;
+  const int nk_row = (K + TT::kStep - 1) / TT::kStep;
+  int L = blockIdx.x;
+  if ((total & 7) == 0) L = (L & 7) * (total >> 3) + (L >> 3);  // contiguous tiles an XCD
+  const int k0 = (int)blockIdx.y * split_steps;
+  const int nk = min(nk_row, k0 + split_steps);
+  const int t0 = (L / nN) * kTM;
+  const int n0 = (L % nN) * kTN;
+
+  // Copy roles.  Activations: copy j = kACopies * wave + jj covers token rows
+  // 4 j' .. 4 j' + 3 of 128 columns (sub-step j / (kTM / 4)), swizzled as in
+  // bingemm_kernel.  Sign words: copy j covers 16 tile rows, four words each.
+  int a_off[TT::kACopies], a_col[TT::kACopies], w_off[TT::kWCopies], w_word[TT::kWCopies];
+#pragma unroll
+  for (int jj = 0; jj < TT::kACopies; ++jj) {
+    const int j = TT::kACopies * wave + jj, sub = j / (kTM / 4);
+    const int tok = 4 * (j % (kTM / 4)) + (lane >> 4);
+    a_col[jj] = 128 * sub + 8 * ((lane & 15) ^ (tok & 15));
+    a_off[jj] = t0 + tok < T ? (t0 + tok) * K * 2 + 2 * a_col[jj] : kOob;
+  }
+#pragma unroll
+  for (int jj = 0; jj < TT::kWCopies; ++jj) {
+    const int j = TT::kWCopies * wave + jj, sub = j / (kTN / 16);
+    const int row = n0 + 16 * (j % (kTN / 16)) + (lane >> 2);
+    w_word[jj] = 4 * sub + (lane & 3);
+    w_off[jj] = row < N ? (row * kw + w_word[jj]) * 4 : kOob;
+  }
+  // Copy c of K step `step` into buffer `buf`; columns past the row, and
+  // steps past the K range, write zeros.
+  const i32x4 a_res = copy_rsrc(A, (int64_t)T * K * 2);
+  const i32x4 w_res = copy_rsrc(W, (int64_t)N * kw * 4);
+  auto copy = [&](auto CI, int step, int buf) {
+    constexpr int c = decltype(CI)::value;
+    const int c0 = step * TT::kStep;
+    const int left = step < nk ? K - c0 : 0;  // uniform
+    uint8_t *base = lds + buf * TT::kStage;
+    if constexpr (c < TT::kACopies)
+      copy16s(a_res, base + (TT::kACopies * wave + c) * 1024, a_col[c] < left ? a_off[c] : kOob,
+              c0 * 2);
+    else
+      copy4s(w_res,
+             base + TT::kSub * TT::kASub + (TT::kWCopies * wave + c - TT::kACopies) * 256,
+             32 * w_word[c - TT::kACopies] < left ? w_off[c - TT::kACopies] : kOob, c0 / 8);
+  };
+  auto issue = [&](int step, int buf) {
+    static_for<TT::kCopies>([&](auto CI) { copy(CI, step, buf); });
+  };
+  // The epilogue's per-token and per-row operands: loaded first, held in
+  // registers over the loop and put in LDS tables behind it, so that no wait
+  // for them stands between the copies.
+  float2 e_ti = make_float2(0.f, 0.f);
+  float e_r = 0.f, smax = 0.f;
+  uint16_t e_rs = 0;
+  float2 gs = make_float2(0.f, 1.f);
+  if constexpr (kMode != kBwdIn) {
+    const int t = min(t0 + (tid & (kTM - 1)), T - 1);
+    e_ti = reinterpret_cast<const float2 *>(tinfo)[t];
+    if constexpr (kFirst) e_r = tinfo_r1(tinfo, T)[t];
+    smax = tinfo[2 * T];
+  }
+  // a tile's tokens share a 64-token scale group
+  if constexpr (kBwd) gs = reinterpret_cast<const float2 *>(gscale)[t0 >> 6];
+  e_rs = rowscale[min(n0 + (tid & (kTN - 1)), N - 1)];
+  // R2 of the tile's tokens: the first product's per-tile row sums, a token
+  // by kPer consecutive lanes, entries part + kPer q
+  constexpr int kPer = TT::kThreads / kTM, kRsRegs = 4;
+  float e_v[kRsRegs] = {};
+  if constexpr (!kBwd && !kFirst) {
+    const float *rr = RS + (size_t)min(t0 + tid / kPer, T - 1) * rs_ld;
+    // (only ranks above kRsRegs kPer tiles loop here, waiting for the loads)
+    for (int b = tid % kPer + kRsRegs * kPer; b < rs_nb; b += kPer) e_r += rr[b];
+#pragma unroll
+    for (int q = 0; q < kRsRegs; ++q) e_v[q] = rr[min(tid % kPer + q * kPer, rs_nb - 1)];
+  }
+  asm volatile("" ::: "memory");  // the loads above are issued here
+#pragma unroll
+  for (int i = 0; i < kS; ++i) issue(k0 + i, i);
+
+  // This wave's operands in 128 columns: activation chunk 2 ks + g of token
+  // row 32 (wt kTB + i) + l mod 32, ks = kNks wk + k; sign words of row
+  // 32 (wr kRB + j) + l mod 32.
+  const int g = lane >> 5;
+  int a_rd[kNks];
+#pragma unroll
+  for (int k = 0; k < kNks; ++k)
+    a_rd[k] = (32 * kTB * wt + (lane & 31)) * 256 +
+              (((2 * (kNks * wk + k) + g) ^ (lane & 15)) << 4);
+  const int w_rd = TT::kSub * TT::kASub + (32 * kRB * wr + (lane & 31)) * 16 + 2 * kNks * wk;
+  int sh[2][4];
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sh[q][e] = 15 - (8 * q + 4 * g + e);
+  const uint32_t rot[2] = {(uint32_t)(4 * g - 10) & 31u, (uint32_t)(8 + 4 * g - 10) & 31u};
+  uint32_t kSignMask;
+  asm volatile("v_mov_b32 %0, 0x80008000" : "=v"(kSignMask));
+
+  floatx16 acc[kTB][kRB];
+#pragma unroll
+  for (int i = 0; i < kTB; ++i)
+#pragma unroll
+    for (int j = 0; j < kRB; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+
+  // Operands of one K step, read from LDS a step ahead: the sign words, then
+  // the activation operands one by one.
+  struct Ops {
+    half8 a[TT::kSub * kNks * kTB];
+    uint32_t w[TT::kSub][kRB][kNks / 2];
+  };
+  constexpr int kReads = 1 + TT::kSub * kNks * kTB;
+  auto read = [&](auto RI, Ops &o, int buf) {
+    constexpr int r = decltype(RI)::value;
+    const uint8_t *base = lds + buf * TT::kStage;
+    if constexpr (r == 0) {
+#pragma unroll
+      for (int sub = 0; sub < TT::kSub; ++sub)
+#pragma unroll
+        for (int j = 0; j < kRB; ++j)
+#pragma unroll
+          for (int q = 0; q < kNks / 2; ++q)
+            o.w[sub][j][q] = *reinterpret_cast<const uint32_t *>(base + w_rd + sub * TT::kWSub +
+                                                                 512 * j + 4 * q);
+    } else {
+      constexpr int n = r - 1, sub = n / (kNks * kTB), k = n / kTB % kNks, i = n % kTB;
+      o.a[n] = *reinterpret_cast<const half8 *>(base + a_rd[k] + sub * TT::kASub + 8192 * i);
+    }
+  };
+  // The sign operand of product group n (sub-step, MFMA step, row block; a
+  // group is kTB MFMAs), as in bingemm_kernel.  Words past the row end are
+  // zero and meet zero activations.
+  constexpr int kGroups = TT::kSub * kNks * kRB;
+  auto expand = [&](auto GI, const Ops &o) {
+    constexpr int n = decltype(GI)::value, sub = n / (kNks * kRB), k = n / kRB % kNks, j = n % kRB;
+    const uint32_t w = o.w[sub][j][k >> 1];
+    uint32_t bd[4];
+    if constexpr (kBwd) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) bd[e] = 0x3c003c00u ^ ((w << sh[k & 1][e]) & kSignMask);
+    } else {
+      const uint32_t wr2 = __builtin_amdgcn_alignbit(w, w, rot[k & 1]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) bd[e] = wr2 & (0x04000400u << e);
+    }
+    return __builtin_bit_cast(half8, make_uint4(bd[0], bd[1], bd[2], bd[3]));
+  };
+  // Step `step` is in `cur`, later ones in LDS or on their way.  After the
+  // barrier step + 1 has landed for every wave, and every wave has read
+  // `step` out of its buffer, which takes step + kS.  The copies, the reads
+  // of step + 1 and the expansion of the next group's signs are issued
+  // behind a group's MFMAs, in their shadow: the waves of a workgroup run in
+  // step, so what stands between the barrier and the first MFMA is time in
+  // which the matrix cores idle (920 -> 650 cycles a 256-column step of 32 x 64).
+  auto run_step = [&](const Ops &cur, Ops &next, int step, int buf) {
+    step_barrier<(kS - 2) * TT::kCopies>();
+    const int nbuf = buf + 1 == kS ? 0 : buf + 1;
+    half8 b = expand(std::integral_constant<int, 0>{}, cur);
+    static_for<kGroups>([&](auto GI) {
+      constexpr int n = decltype(GI)::value, sub = n / (kNks * kRB), k = n / kRB % kNks,
+                    j = n % kRB;
+#pragma unroll
+      for (int i = 0; i < kTB; ++i)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cur.a[(sub * kNks + k) * kTB + i], b,
+                                                           acc[i][j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (n + 1 < kGroups) b = expand(std::integral_constant<int, n + 1>{}, cur);
+      constexpr int kOps = kReads + TT::kCopies;
+      static_for<kOps>([&](auto OI) {
+        constexpr int o = decltype(OI)::value;
+        if constexpr (o * kGroups / kOps == n) {
+          if constexpr (o < kReads) read(OI, next, nbuf);
+          else copy(std::integral_constant<int, o - kReads>{}, step + kS, buf);
+        }
+      });
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  // (a pair of steps an iteration; a step past the range adds zeros)
+  Ops o0, o1;
+  step_barrier<(kS - 1) * TT::kCopies>();
+  static_for<kReads>([&](auto RI) { read(RI, o0, 0); });
+  int buf = 0;
+  for (int step = k0; step < nk; step += 2) {
+    run_step(o0, o1, step, buf);
+    buf = buf + 1 == kS ? 0 : buf + 1;
+    run_step(o1, o0, step + 1, buf);
+    buf = buf + 1 == kS ? 0 : buf + 1;
+  }
+
+  // The wave tiles go to LDS (fp32, natural order, one copy per wk), and a
+  // thread adds and finishes 8 positions of a token at a time.
+  step_barrier<0>();  // the copies past the K range write zeros into the stages
+  float *red = reinterpret_cast<float *>(lds);
+#pragma unroll
+  for (int i = 0; i < kTB; ++i)
+#pragma unroll
+    for (int j = 0; j < kRB; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        red[(wk * kTM + 32 * (kTB * wt + i) + 8 * (e >> 2) + 4 * g + (e & 3)) * TT::kRedLd +
+            32 * (kRB * wr + j) + (lane & 31)] = acc[i][j][e];
+  float2 *tab_ti = reinterpret_cast<float2 *>(lds + TT::kTab);
+  float *tab_r = reinterpret_cast<float *>(tab_ti + kTM);
+  uint16_t *tab_rs = reinterpret_cast<uint16_t *>(tab_r + kTM);
+  if (tid < kTM) {
+    if constexpr (kMode != kBwdIn) tab_ti[tid] = e_ti;
+    if constexpr (kFirst) tab_r[tid] = e_r;
+  }
+  if (tid < kTN) tab_rs[tid] = n0 + tid < N ? e_rs : (uint16_t)0;
+  if constexpr (!kBwd && !kFirst) {
+    // added in a fixed order; the first column tile and K range also stores
+    // R2 for the split-K reduction
+    const int tok = tid / kPer, part = tid % kPer;
+#pragma unroll
+    for (int q = 0; q < kRsRegs; ++q) e_r += part + q * kPer < rs_nb ? e_v[q] : 0.f;
+#pragma unroll
+    for (int o = 1; o < kPer; o <<= 1) e_r += __shfl_xor(e_r, o, 64);
+    if (part == 0) {
+      tab_r[tok] = e_r;
+      if (gridDim.y > 1 && n0 == 0 && k0 == 0 && t0 + tok < T) tinfo_r2(tinfo, T)[t0 + tok] = e_r;
+    }
+  }
+  lds_barrier();
+  constexpr int kUpr = kTN / 8;  // units a token row
+  constexpr int kUnits = kTM * kUpr;
+  float bwd_g[(kUnits + TT::kThreads - 1) / TT::kThreads][8];
+  (void)bwd_g;
+#pragma unroll
+  for (int it = 0; it < (kUnits + TT::kThreads - 1) / TT::kThreads; ++it) {
+    const int u = it * TT::kThreads + tid;
+    if (kUnits % TT::kThreads != 0 && u >= kUnits) break;  // whole waves
+    const int row = u / kUpr, ps = (u % kUpr) * 8;
+    const int t = t0 + row, p = n0 + ps;
+    const bool live = t < T && p < N;
+    int cl, ch;  // tile columns of the two float4 runs
+    if (kPairOut) {
+      cl = (ps & ~31) + ((ps & 31) >> 1);
+      ch = cl + 16;
+    } else {
+      cl = ps;
+      ch = ps + 4;
+    }
+    float4 lo = make_float4(0.f, 0.f, 0.f, 0.f), hi = lo;
+#pragma unroll
+    for (int q = 0; q < TT::kWK; ++q) {
+      const float *r = red + (q * kTM + row) * TT::kRedLd;
+      const float4 a = *reinterpret_cast<const float4 *>(r + cl);
+      const float4 b = *reinterpret_cast<const float4 *>(r + ch);
+      lo.x += a.x; lo.y += a.y; lo.z += a.z; lo.w += a.w;
+      hi.x += b.x; hi.y += b.y; hi.z += b.z; hi.w += b.w;
+    }
+    if (gridDim.y > 1) {  // uniform
+      if (live) {
+        float *d = P + ((size_t)blockIdx.y * T + t) * N + n0;
+        *reinterpret_cast<float4 *>(d + cl) = lo;
+        *reinterpret_cast<float4 *>(d + ch) = hi;
+      }
+      continue;
+    }
+    Fin8In in;
+    in.ti = tab_ti[row];
+    in.smax = smax;
+    in.rt = tab_r[row];
+    in.rlo = *reinterpret_cast<const uint2 *>(tab_rs + cl);
+    in.rhi = *reinterpret_cast<const uint2 *>(tab_rs + ch);
+    if constexpr (kBwd) {
+      const uint4 sq = live ? *reinterpret_cast<const uint4 *>(S + (size_t)t * N + p)
+                            : make_uint4(0u, 0u, 0u, 0u);
+      const uint4 c = bwd_finish8<kMode>(lo, hi, in, gs, sq, bwd_g[it]);
+      if (C && live) *reinterpret_cast<uint4 *>(C + (size_t)t * N + p) = c;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) bwd_g[it][e] = live ? bwd_g[it][e] : 0.f;
+    } else {
+      float a = finish8<kMode>(lo, hi, in, live ? p : 0, t, N, C, V, F, live);
+      if constexpr (kFirst) {
+        // the token's row sum over the tile, kUpr consecutive lanes
+#pragma unroll
+        for (int o = 1; o < kUpr; o <<= 1) a += __shfl_xor(a, o, 64);
+        if (ps == 0 && t < T) RS[(size_t)t * rs_ld + n0 / kTN] = a;
+      }
+    }
+  }
+  if constexpr (kBwd) {
+    if (gridDim.y > 1) return;
+    // token sums of gradient * S, in token order
+    lds_barrier();  // every thread has read its sums
+#pragma unroll
+    for (int it = 0; it < (kUnits + TT::kThreads - 1) / TT::kThreads; ++it) {
+      const int u = it * TT::kThreads + tid;
+      if (kUnits % TT::kThreads != 0 && u >= kUnits) break;
+      float *d = red + (u / kUpr) * TT::kRedLd + (u % kUpr) * 8;
+      *reinterpret_cast<float4 *>(d) =
+          make_float4(bwd_g[it][0], bwd_g[it][1], bwd_g[it][2], bwd_g[it][3]);
+      *reinterpret_cast<float4 *>(d + 4) =
+          make_float4(bwd_g[it][4], bwd_g[it][5], bwd_g[it][6], bwd_g[it][7]);
+    }
+    lds_barrier();
+    if (tid < kTN && n0 + tid < N) {
+      float sum = 0.f;
+#pragma unroll 8
+      for (int k = 0; k < kTM; ++k) sum += red[k * TT::kRedLd + tid];
+      const int pp = n0 + tid;
+      const int n = kPairOut ? (pp & ~31) + ((pp & 31) >> 1) + 16 * (pp & 1) : pp;
+      F[(size_t)(t0 / kTM) * N + n] = sum;
+    }
+  }
+}
+
+using Tok64 = TokTile<64, 128, 2, 2, 2, 1, 4>;
+using Tok32w = TokTile<32, 128, 1, 4, 2, 2, 3>;
+using Tok32 = TokTile<32, 64, 1, 2, 4, 2, 4>;
+
+
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 // Copy pipeline depth per token-tile height.
@@ -1810,7 +2236,8 @@ size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 constexpr int kStages128 = AF1_GEMM_STAGES_128;
 constexpr int kStages64 = AF1_GEMM_STAGES_64;
 
-// How one contraction is launched.  A grid of 128-token tiles that gives
+// How one contraction is launched: by tokgemm_kernel's small tiles, or by
+// bingemm_kernel as follows.  A grid of 128-token tiles that gives
 // each compute unit at most one workgroup (one wave per SIMD) uses 64-token
 // tiles instead: twice the workgroups, each expanding its signs for half as
 // many tokens (measured on 8192x8192 G1: +2%; grids between one and two
@@ -1829,6 +2256,7 @@ constexpr int kMinSplitSteps = 2;
 constexpr double kStepUs = 1.5, kPartialBytesPerUs = 4.0e6, kLaunchUs = 3.0;
 struct ContractionPlan {
   int bm;                // token-tile height
+  int bn;                // weight rows a tile: BN is bingemm_kernel, others tokgemm_kernel
   unsigned gx, gy;       // weight-row tiles, token tiles
   int splits, split_steps;
   int mix_full, mix_splits;  // mixed grid (mix_full > 0): whole tiles, K ranges per other tile
@@ -1845,10 +2273,47 @@ struct ContractionPlan {
 constexpr int kMixSplits = 3;
 constexpr int kMixMinSteps = 24;
 
+// Estimated time (us) of a contraction on `wgs` workgroups of `steps` K steps
+// each: a fixed part; per step the larger (as a fourth-power mean) of t1, what
+// a step takes a workgroup alone on its unit (latency), and tp for every
+// workgroup a unit has to carry (throughput, at the clock the power limit
+// leaves); and for a split K the reduction launch and its traffic.
+struct StepCost {
+  double fixed, t1, tp, reduce, per_mb;
+};
+double contraction_us(const StepCost &c, double wgs, int64_t steps, int64_t splits, int64_t T,
+                      int64_t N, int cus) {
+  double load = wgs / cus;  // workgroups a unit; past one, halfway to the last full round
+  if (load > 1.0) load = 0.5 * (load + ceil(load));
+  const double a = c.t1 * c.t1, b = load * c.tp * load * c.tp;
+  double us = c.fixed + (double)steps * sqrt(sqrt(a * a + b * b));
+  if (splits > 1) us += c.reduce + c.per_mb * (double)splits * T * N * 4e-6;
+  return us;
+}
+// Least-squares fits to kernel-trace durations of both products of eight
+// layer shapes (1024^2 to 28672x8192) at 17 to 2048 tokens: within 6-10% rms.
+// The choices made from them were never more than 2% slower than
+// bingemm_kernel on those 160 contractions, 27% faster in the mean, and within
+// 1.3% of the best choice in the mean.
+constexpr StepCost kCost64 = {5.3, 0.91, 0.80, 3.7, 0.31};   // bingemm_kernel, 64 x 256
+constexpr StepCost kCost128 = {5.3, 0.0, 1.59, 3.7, 0.31};   // and 128 x 256
+constexpr double kMixedUs = 11.7;                            // a mixed grid's reduction
+struct TokShape {
+  int bm, bn, step;  // tile, columns of a K step
+  int max_splits;
+  StepCost cost;
+};
+constexpr TokShape kTokShapes[] = {
+    {Tok64::kTM, Tok64::kTN, Tok64::kStep, 1, {4.3, 0.397, 0.486, 0.0, 0.0}},
+    {Tok32w::kTM, Tok32w::kTN, Tok32w::kStep, 2, {4.0, 0.432, 0.543, 3.0, 0.43}},
+    {Tok32::kTM, Tok32::kTN, Tok32::kStep, 4, {4.3, 0.274, 0.332, 2.3, 0.74}},
+};
+
 ContractionPlan plan_contraction(int64_t T, int64_t K, int64_t N, bool allow_split, int cus,
                                  bool allow_mixed = false) {
   ContractionPlan p;
   p.mix_full = p.mix_splits = 0;
+  p.bn = BN;
   p.gx = (unsigned)((N + BN - 1) / BN);
   const int64_t tiles128 = (int64_t)p.gx * ((T + BM - 1) / BM);
   p.bm = tiles128 <= (int64_t)cus ? 64 : BM;
@@ -1879,8 +2344,31 @@ ContractionPlan plan_contraction(int64_t T, int64_t K, int64_t N, bool allow_spl
     p.split_steps = (int)((nk + kMixSplits - 1) / kMixSplits);
     p.mix_splits = (int)((nk + p.split_steps - 1) / p.split_steps);
   }
+  // tokgemm_kernel where its estimate is lower, each tile with 1, 2 or 4 K
+  // ranges as far as they paid
+  const bool mixed = p.mix_full > 0;
+  double best = contraction_us(p.bm == BM ? kCost128 : kCost64, (double)tiles * p.splits,
+                               mixed ? nk : p.split_steps, p.splits, T, N, cus) +
+                (mixed ? kMixedUs : 0.0);
+  for (const TokShape &c : kTokShapes) {
+    const int64_t gx = (N + c.bn - 1) / c.bn, gy = (T + c.bm - 1) / c.bm;
+    const int64_t nks = (K + c.step - 1) / c.step;
+    for (int64_t sp = 1; sp <= (allow_split ? c.max_splits : 1); sp *= 2) {
+      const int64_t steps = (nks + sp - 1) / sp, n = (nks + steps - 1) / steps;
+      const double us = contraction_us(c.cost, (double)(gx * gy * n), steps, n, T, N, cus);
+      if (us >= best) continue;
+      best = us;
+      p = ContractionPlan{c.bm, c.bn, (unsigned)gx, (unsigned)gy, (int)n, (int)steps, 0, 0};
+    }
+  }
   return p;
 }
+
+// Columns an entry of RS covers after a first product with this plan (the
+// split-K reduction's rows of 256), and the tokens a row of F covers after a
+// backward one.
+int rs_width(const ContractionPlan &p) { return p.splits > 1 ? 256 : p.bn; }
+int f_tokens(const ContractionPlan &p) { return p.splits > 1 ? 64 : p.bm; }
 
 size_t mixed_bytes(const ContractionPlan &p, int64_t T, int64_t N) {
   if (p.mix_full == 0) return 0;
@@ -1904,24 +2392,44 @@ hipError_t contraction(const uint16_t *A, int64_t T, int64_t K, const uint32_t *
                        const uint16_t *rs, uint16_t *C, uint16_t *V, const uint16_t *S,
                        float *F, hipStream_t s, int *tile_tokens = nullptr,
                        const float *gscale = nullptr, float *P = nullptr,
-                       const float *tinfo_in = nullptr, float *RS = nullptr) {
+                       const float *tinfo_in = nullptr, float *RS = nullptr, int rs_w = 0) {
   float *tinfo = const_cast<float *>(tinfo_in);
   constexpr bool kFwd = kMode == kMid || kMode == kMidSave || kMode == kOut || kMode == kOutSave;
   const ContractionPlan p = plan_contraction(T, K, N, P != nullptr, device_cus(), kFwd && P);
-  if (p.splits > 1 && p.bm != 64) return hipErrorInvalidValue;  // see bingemm_kernel
+  if (p.splits > 1 && p.bn == BN && p.bm != 64) return hipErrorInvalidValue;  // see bingemm_kernel
   const int64_t tiles = (int64_t)p.gx * p.gy;
   const dim3 g = p.mix_full > 0
                      ? dim3((unsigned)(p.mix_full + (tiles - p.mix_full) * p.mix_splits))
                      : dim3(p.gx, p.gy, (unsigned)p.splits);
-  if (p.bm == 64)
+  // RS entries a token (the second product's; the first writes its own) and
+  // their row length
+  constexpr bool kFirst = kMode == kMid || kMode == kMidSave;
+  const int w = kFirst ? rs_width(p) : rs_w;
+  const int64_t rw = kFirst ? N : K;  // the intermediate's width
+  const int nb = w > 0 ? (int)((rw + w - 1) / w) : 0, ld = w > 0 ? rs_ld(rw, w) : 0;
+  if (p.bn != BN) {
+    const dim3 gt((unsigned)tiles, (unsigned)p.splits);
+    auto go = [&](auto tile) {
+      using TT = decltype(tile);
+      tokgemm_kernel<kMode, TT><<<gt, TT::kThreads, TT::kBytes, s>>>(
+          A, W, (int)T, (int)K, (int)N, (int)p.gx, (int)tiles, p.split_steps, rs, tinfo, RS,
+          gscale, nb, ld, C, V, S, F, P);
+    };
+    if (p.bm == 64)
+      go(Tok64{});
+    else if (p.bn == 128)
+      go(Tok32w{});
+    else
+      go(Tok32{});
+  } else if (p.bm == 64)
     bingemm_kernel<kMode, 64, kStages64><<<g, kThreads, Lds<64, kStages64>::kBytes, s>>>(
         A, (int)T, (int)K, W, (int)N, rs, C, V, S, F, gscale, p.split_steps, P, p.mix_full,
-        p.mix_splits, (int)p.gx, tinfo, RS);
+        p.mix_splits, (int)p.gx, tinfo, RS, nb, ld);
   else
     bingemm_kernel<kMode, BM, kStages128><<<g, kThreads, Lds<BM, kStages128>::kBytes, s>>>(
         A, (int)T, (int)K, W, (int)N, rs, C, V, S, F, gscale, p.split_steps, P, p.mix_full,
-        p.mix_splits, (int)p.gx, tinfo, RS);
-  if (tile_tokens) *tile_tokens = p.splits > 1 ? 64 : p.bm;
+        p.mix_splits, (int)p.gx, tinfo, RS, nb, ld);
+  if (tile_tokens) *tile_tokens = f_tokens(p);
   if (p.mix_full > 0) {
     if constexpr (kFwd) {
       const unsigned blocks = (unsigned)((tiles - p.mix_full) * 16);
@@ -2006,7 +2514,18 @@ hipError_t prepare_forward(int64_t n, const uint16_t *s_in, const uint16_t *x, i
 
 size_t tinfo_bytes(int64_t T) { return align256((size_t)tinfo_floats(T) * 4); }
 
-size_t rowsum_bytes(int64_t r, int64_t T) { return align256((size_t)T * rs_ld(r) * 4); }
+size_t rowsum_bytes(int64_t r, int64_t T, int rs_w) {
+  return align256((size_t)T * rs_ld(r, rs_w) * 4);
+}
+
+// The plans of the forward's two contractions.
+struct FwdPlans {
+  ContractionPlan g1, g2;
+};
+FwdPlans forward_plans(int64_t m, int64_t n, int64_t r, int64_t T, int cus) {
+  return FwdPlans{plan_contraction(T, n, r, true, cus, true),
+                  plan_contraction(T, r, m, true, cus, true)};
+}
 
 struct FwdWs {
   uint16_t *xp, *Z;
@@ -2015,7 +2534,7 @@ struct FwdWs {
   float *P;      // split-K partials of G1 or G2 (one at a time)
 };
 
-FwdWs forward_ws(void *ws, int64_t n, int64_t r, int64_t T) {
+FwdWs forward_ws(void *ws, int64_t n, int64_t r, int64_t T, int rs_w) {
   uint8_t *base = static_cast<uint8_t *>(ws);
   FwdWs w;
   w.xp = reinterpret_cast<uint16_t *>(base);
@@ -2025,7 +2544,7 @@ FwdWs forward_ws(void *ws, int64_t n, int64_t r, int64_t T) {
   w.tinfo = reinterpret_cast<float *>(base);
   base += tinfo_bytes(T);
   w.RS = reinterpret_cast<float *>(base);
-  base += rowsum_bytes(r, T);
+  base += rowsum_bytes(r, T, rs_w);
   w.P = reinterpret_cast<float *>(base);
   return w;
 }
@@ -2037,7 +2556,20 @@ struct BwdWs {
   float *p_out, *p_mid, *p_in, *tstat, *gscale, *P;
 };
 
+// Rows of the per-tile token sums of the two backward contractions.
+struct BwdTiles {
+  ContractionPlan b1, b2;
+  int64_t f1, f2;
+};
+BwdTiles backward_tiles(int64_t m, int64_t n, int64_t r, int64_t T, int cus) {
+  BwdTiles b{plan_contraction(T, m, r, true, cus), plan_contraction(T, r, n, true, cus), 0, 0};
+  b.f1 = (T + f_tokens(b.b1) - 1) / f_tokens(b.b1);
+  b.f2 = (T + f_tokens(b.b2) - 1) / f_tokens(b.b2);
+  return b;
+}
+
 BwdWs backward_ws(void *ws, int64_t m, int64_t n, int64_t r, int64_t T) {
+  const BwdTiles bt = backward_tiles(m, n, r, T, device_cus());
   uint8_t *base = static_cast<uint8_t *>(ws);
   BwdWs w;
   w.A1 = reinterpret_cast<uint16_t *>(base);
@@ -2047,9 +2579,9 @@ BwdWs backward_ws(void *ws, int64_t m, int64_t n, int64_t r, int64_t T) {
   w.p_out = reinterpret_cast<float *>(base);
   base += align256((size_t)tiles64(T) * m * 4);
   w.p_mid = reinterpret_cast<float *>(base);
-  base += align256((size_t)tiles64(T) * r * 4);
+  base += align256((size_t)bt.f1 * r * 4);
   w.p_in = reinterpret_cast<float *>(base);
-  base += align256((size_t)tiles64(T) * n * 4);
+  base += align256((size_t)bt.f2 * n * 4);
   w.tstat = reinterpret_cast<float *>(base);
   base += align256((size_t)T * 8 + 4);
   w.gscale = reinterpret_cast<float *>(base);
@@ -2060,12 +2592,11 @@ BwdWs backward_ws(void *ws, int64_t m, int64_t n, int64_t r, int64_t T) {
 
 size_t backward_ws_bytes(int64_t m, int64_t n, int64_t r, int64_t T) {
   // ... and the fp32 partials of whichever backward contraction splits K
-  const int cus = device_cus();
-  const size_t p1 = split_bytes(plan_contraction(T, m, r, true, cus), T, r);
-  const size_t p2 = split_bytes(plan_contraction(T, r, n, true, cus), T, n);
+  const BwdTiles bt = backward_tiles(m, n, r, T, device_cus());
+  const size_t p1 = split_bytes(bt.b1, T, r), p2 = split_bytes(bt.b2, T, n);
   return align256((size_t)T * m * 2) + align256((size_t)T * r * 2) +
-         align256((size_t)tiles64(T) * m * 4) + align256((size_t)tiles64(T) * r * 4) +
-         align256((size_t)tiles64(T) * n * 4) + align256((size_t)T * 8 + 4) +
+         align256((size_t)tiles64(T) * m * 4) + align256((size_t)bt.f1 * r * 4) +
+         align256((size_t)bt.f2 * n * 4) + align256((size_t)T * 8 + 4) +
          align256((size_t)tiles64(T) * 8) + (p1 > p2 ? p1 : p2);
 }
 
@@ -2075,14 +2606,14 @@ size_t gemm_workspace_bytes(int64_t m, int64_t n, int64_t r, int64_t T) {
   // fp16(s_in .* x) and the fp16 intermediate Z, both in pair order, and the
   // fp32 partials of whichever contraction splits its K steps
   const int cus = device_cus();
-  const ContractionPlan g1 = plan_contraction(T, n, r, true, cus, true);
-  const ContractionPlan g2 = plan_contraction(T, r, m, true, cus, true);
+  const FwdPlans fp = forward_plans(m, n, r, T, cus);
+  const ContractionPlan &g1 = fp.g1, &g2 = fp.g2;
   const size_t p1 = split_bytes(g1, T, r) > mixed_bytes(g1, T, r) ? split_bytes(g1, T, r)
                                                                    : mixed_bytes(g1, T, r);
   const size_t p2 = split_bytes(g2, T, m) > mixed_bytes(g2, T, m) ? split_bytes(g2, T, m)
                                                                    : mixed_bytes(g2, T, m);
   return align256((size_t)T * (size_t)n * 2) + align256((size_t)T * (size_t)r * 2) +
-         tinfo_bytes(T) + rowsum_bytes(r, T) + (p1 > p2 ? p1 : p2);
+         tinfo_bytes(T) + rowsum_bytes(r, T, rs_width(g1)) + (p1 > p2 ? p1 : p2);
 }
 
 hipError_t launch_gemm(int64_t m, int64_t n, int64_t r, const uint32_t *Bu,
@@ -2094,14 +2625,15 @@ hipError_t launch_gemm(int64_t m, int64_t n, int64_t r, const uint32_t *Bu,
   if (T * n * 2 > 0x7fffffff || T * r * 2 > 0x7fffffff || m * (r / 32) * 4 > 0x7fffffff ||
       r * (n / 32) * 4 > 0x7fffffff)
     return hipErrorInvalidValue;
-  const FwdWs w = forward_ws(ws, n, r, T);
+  const int rs_w = rs_width(plan_contraction(T, n, r, true, device_cus(), true));
+  const FwdWs w = forward_ws(ws, n, r, T, rs_w);
   hipError_t e = prepare_forward(n, s_in, x, T, w.xp, w.tinfo, s_mid, r, s);
   if (e != hipSuccess) return e;
   e = contraction<kMid>(w.xp, T, n, Bv, r, s_mid, w.Z, nullptr, nullptr, nullptr, s, nullptr,
-                        nullptr, w.P, w.tinfo, w.RS);
+                        nullptr, w.P, w.tinfo, w.RS, rs_w);
   if (e != hipSuccess) return e;
   return contraction<kOut>(w.Z, T, r, Bu, m, s_out, y, nullptr, nullptr, nullptr, s, nullptr,
-                           nullptr, w.P, w.tinfo, w.RS);
+                           nullptr, w.P, w.tinfo, w.RS, rs_w);
 }
 
 size_t train_saved_bytes(int64_t m, int64_t n, int64_t r, int64_t T) {
@@ -2125,7 +2657,8 @@ hipError_t launch_forward_train(int64_t m, int64_t n, int64_t r, const uint32_t 
   if (T * n * 2 > 0x7fffffff || T * r * 2 > 0x7fffffff || m * (r / 32) * 4 > 0x7fffffff ||
       r * (n / 32) * 4 > 0x7fffffff)
     return hipErrorInvalidValue;
-  const FwdWs w = forward_ws(ws, n, r, T);
+  const int rs_w = rs_width(plan_contraction(T, n, r, true, device_cus(), true));
+  const FwdWs w = forward_ws(ws, n, r, T, rs_w);
   uint16_t *v = static_cast<uint16_t *>(saved);
   float *z = reinterpret_cast<float *>(static_cast<uint8_t *>(saved) + align256((size_t)T * r * 2));
   float *tinfo = reinterpret_cast<float *>(static_cast<uint8_t *>(saved) +
@@ -2136,10 +2669,10 @@ hipError_t launch_forward_train(int64_t m, int64_t n, int64_t r, const uint32_t 
   // the same G1 as the inference forward, which also keeps fp16(v) at the
   // token's scale
   e = contraction<kMidSave>(w.xp, T, n, Bv, r, s_mid, w.Z, v, nullptr, nullptr, s, nullptr,
-                            nullptr, w.P, tinfo, w.RS);
+                            nullptr, w.P, tinfo, w.RS, rs_w);
   if (e != hipSuccess) return e;
   return contraction<kOutSave>(w.Z, T, r, Bu, m, s_out, y, nullptr, nullptr, z, s, nullptr,
-                               nullptr, w.P, tinfo, w.RS);
+                               nullptr, w.P, tinfo, w.RS, rs_w);
 }
 
 hipError_t launch_backward(int64_t m, int64_t n, int64_t r, const uint32_t *BuT,
