@@ -214,6 +214,87 @@ __device__ __forceinline__ void store_unit(uint8_t *slot_base, int h, const floa
   slot[4 * h + 3] = make_uint4(lo[4], lo[5], lo[6], lo[7]);
 }
 
+// The link: how the two stages of a layer meet in one launch.  The first
+// stage's workgroups come first in the grid and wait for nothing; the
+// second's load their sign words and wait for the intermediate, word by word:
+// a word of a link buffer is zero until its value is stored there (a value of
+// +0 is stored as -0), so the data is its own flag and the hand-off costs one
+// store and one load, where a kernel boundary costs the first kernel's last
+// store, about 1.1 us, and the second's cold start.
+//
+// There are two buffers.  A call uses the one of its number's parity and
+// clears the other (whose readers ended with the call before).  The number is
+// drawn by an atomic add a workgroup on one of 16 words (64 bits, their own
+// cache lines): the first workgroup of a word adds what makes its adds of this
+// call 2^20 in all, so every workgroup of call k reads k in the upper bits.
+//
+// Both lie in the workspace header, which is zero before the first use, past
+// the last-slab counters: a stage has at most 2^16 row tiles and gives a
+// workgroup 8 of them once they exceed two workgroups a unit, so at most 8192
+// counters (kMaxCounters) of the 2^16 words of each half are in use.
+constexpr int kLinkNone = 0, kLinkOut = 1, kLinkIn = 2;
+constexpr int kHeaderHalf = 1 << 16;    // words of half the header
+constexpr int kMaxCounters = 8192;      // last-slab counters of a stage
+constexpr int kLinkSlots = 16, kLinkSlotWords = 32;
+constexpr int kLinkTickets = kMaxCounters;  // word offset in the first half
+constexpr int kLinkData = kLinkTickets + kLinkSlots * kLinkSlotWords;  // in each half
+constexpr int kLinkWords = kHeaderHalf - kLinkData;
+// Polls (about a microsecond each) before giving up with NaN.  A first-stage
+// workgroup may have to wait for another stream's kernel to leave its units
+// while second-stage ones already poll elsewhere, so the limit is far above
+// any kernel's time.
+constexpr int kLinkSpins = 1 << 24;
+constexpr uint32_t kLinkNan = 0x7fc00000u;
+
+__device__ __forceinline__ void store_device_word(uint32_t *p, uint32_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// This call's buffer (0 or 1); one thread of every workgroup of the grid.
+__device__ __forceinline__ int link_ticket(uint32_t *hdr, int grid) {
+  const int slot = (int)blockIdx.x & (kLinkSlots - 1);
+  const int n = (grid - slot + kLinkSlots - 1) / kLinkSlots;  // workgroups of this slot
+  const unsigned long long add =
+      (int)blockIdx.x < kLinkSlots ? (1ull << 20) - (unsigned long long)(n - 1) : 1ull;
+  unsigned long long *t =
+      reinterpret_cast<unsigned long long *>(hdr + kLinkTickets + slot * kLinkSlotWords);
+  return (int)(__hip_atomic_fetch_add(t, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 20) &
+         1;
+}
+
+__device__ __forceinline__ uint32_t *link_buffer(uint32_t *hdr, int buf) {
+  return hdr + buf * kHeaderHalf + kLinkData;
+}
+
+// A zero that the compiler cannot see through: added to the address of a
+// polled load, it makes every poll a load of its own.  (The buffer loads are
+// read-only to the compiler, which may otherwise take them out of the loop.)
+__device__ __forceinline__ int fresh_zero() {
+  int z = 0;
+  asm volatile("" : "+s"(z));
+  return z;
+}
+
+// Waits until any of the wave's words (a lane's byte offset off, kOob for none)
+// is set: a light poll in front of the real loads, so that waiting waves leave
+// the memory path to the first stage, until its first values arrive.  False after kLinkSpins polls.
+__device__ __forceinline__ bool link_probe(__amdgpu_buffer_rsrc_t res, int off) {
+  for (int it = 0; it < kLinkSpins; ++it) {
+    const uint32_t v = __builtin_amdgcn_raw_buffer_load_b32(res, off, fresh_zero(), kDeviceScope);
+    if (__any(v != 0u) || __all(off == kOob)) return true;
+    __builtin_amdgcn_s_sleep(1);
+  }
+  return false;
+}
+
+// Workgroup blk of blks clears its share of a link buffer.
+__device__ __forceinline__ void link_clear(uint32_t *buf, int blk, int blks) {
+  uint4 *p = reinterpret_cast<uint4 *>(buf);
+  for (int i = blk * (int)blockDim.x + (int)threadIdx.x; i < kLinkWords / 4;
+       i += blks * (int)blockDim.x)
+    p[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
 // Output modes of a stage launch.
 constexpr int kModeFinal = 0;     // one slab: write the scaled result
 constexpr int kModeLastSlab = 1;  // several slabs: the last one to finish adds them
@@ -320,19 +401,24 @@ __device__ __forceinline__ void stage_signs(SignRegs &sg, const uint32_t *__rest
   }
 }
 
+// kLink: the two stages of a layer in one launch (gemv_fused_kernel), the
+// intermediate passed through the link (see LinkHeader): kLinkOut stores it
+// there, kLinkIn waits for it there.
 // kLoop: a wave may own more than kMaxGroups groups; they are taken in
 // chunks of kMaxGroups, the next chunk's sign words loading while the
 // current chunk's products run (the stream kernel, whose persistent
 // workgroups cover long rows without splitting them into slabs).
 template <bool kInX, bool kOutY, bool kHiLoCols, bool kMulti, bool kCoherent = false,
-          bool kLoop = false>
+          bool kLoop = false, int kLink = kLinkNone>
 __device__ __forceinline__ void stage_body(
     const uint32_t *__restrict__ M, const void *__restrict__ in,
     const uint16_t *__restrict__ s_in, const uint16_t *__restrict__ row_scale, int rows,
     int wpr, int slab_words, int b, int rt_log2_arg, int nslabs, int mode, int in_parts,
     void *__restrict__ out, float *__restrict__ part, uint32_t *__restrict__ cnt, int group,
-    int slab, int red_off = 0, const SignRegs *pre = nullptr) {
-  constexpr int kInAux = kCoherent ? kDeviceScope : 0;
+    int slab, int red_off = 0, const SignRegs *pre = nullptr, uint32_t *link = nullptr,
+    int link_grid = 0, int link_blk = 0, int link_blks = 0) {
+  constexpr int kInAux = kCoherent || kLink == kLinkIn ? kDeviceScope : 0;
+  __shared__ int s_link;  // this call's link buffer
   const int rt_log2 = kMulti ? rt_log2_arg : 0;
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   const int tid = threadIdx.x;
@@ -382,6 +468,21 @@ __device__ __forceinline__ void stage_body(
     load_chunk(wv, 0);
   };
 
+  uint32_t rscale_bits[kMaxOutPerThread];
+  if constexpr (kLink == kLinkIn) {
+    // The weights do not depend on the first product: they travel while it
+    // runs, but behind the ticket, so that the first product's own loads go
+    // first.  The buffer that the call before used is cleared for the next.
+    if (tid == 0) s_link = link_ticket(link, link_grid);
+    __syncthreads();
+    load_signs();
+    load_row_scales(rscale_bits, row_scale, rows, group, rt_log2, b,
+                    kMulti ? (((16 << rt_log2) * b + kThreads - 1) / kThreads) : 1);
+    uint32_t *mine = link_buffer(link, s_link);
+    link_clear(link_buffer(link, s_link ^ 1), link_blk, link_blks);
+    in = mine;
+  }
+
   // 2. Stage the input columns as bf16 hi/lo (p, p+16) pairs, one 144-byte
   //    slot per (batch row, word); slot 0 holds zeros for lanes with no
   //    batch row and for the tail of a ragged group.  A unit is 8 columns
@@ -396,6 +497,7 @@ __device__ __forceinline__ void stage_body(
   //    scratch slot instead of branching, so that no load is moved behind
   //    another unit's wait.
   uint8_t *xs = lds + kSlot;
+  int ticket = 0;  // kLinkOut, thread 0
   // Every wave writes the zero slot itself: with one tile per workgroup no
   // barrier separates staging from the products, and a wave whose ragged
   // group tail points at the slot must see zeros written in its own program
@@ -414,7 +516,62 @@ __device__ __forceinline__ void stage_body(
     const bool two_parts = !kInX && in_parts > 1;
     const int bstride = row_stride(w_count);
     uint8_t *junk = xs + (size_t)b * bstride + (tid & 15) * kSlot;
-    if (kHiLoCols && !shared && b == 1) {
+    if constexpr (kLink == kLinkIn) {
+      // One batch row and one tile (the rule for one launch): the quarter
+      // units below, from the link, again until every value of the wave's
+      // columns is there.
+      const int rem = lane >> 2, qq = lane & 3;
+      auto column = [&](int i) {  // the lane's first column of group i, -1 for none
+        const int wl = (R.cw + R.wpt * i) * kGroupWords + (rem >> 1);
+        return wl < w_count ? (w_begin + wl) * 32 + 8 * (rem & 1) + 2 * qq : -1;
+      };
+      int spins = link_probe(xres, column(0) >= 0 ? column(0) * 4 : kOob) ? 0 : kLinkSpins;
+      for (;; ++spins) {
+        const int z = fresh_zero();
+        u32x2 ra[kMaxGroups], rb[kMaxGroups], rc[kMaxGroups], rd[kMaxGroups];
+#pragma unroll
+        for (int i = 0; i < kMaxGroups; ++i) {
+          if (i >= R.my_groups) break;  // uniform
+          const int col = column(i);
+          const int to = col >= 0 ? col * 4 : kOob;
+          ra[i] = __builtin_amdgcn_raw_buffer_load_b64(xres, to, z, kInAux);
+          rb[i] = __builtin_amdgcn_raw_buffer_load_b64(xres, to + 64, z, kInAux);
+          if (two_parts) {
+            const int to2 = col >= 0 ? (col + part_elems) * 4 : kOob;
+            rc[i] = __builtin_amdgcn_raw_buffer_load_b64(xres, to2, z, kInAux);
+            rd[i] = __builtin_amdgcn_raw_buffer_load_b64(xres, to2 + 64, z, kInAux);
+          }
+        }
+        bool there = true;
+#pragma unroll
+        for (int i = 0; i < kMaxGroups; ++i) {
+          if (i >= R.my_groups) break;  // uniform
+          const int col = column(i);
+          bool set = ra[i][0] != 0u && ra[i][1] != 0u && rb[i][0] != 0u && rb[i][1] != 0u;
+          float v[4] = {__uint_as_float(ra[i][0]), __uint_as_float(ra[i][1]),
+                        __uint_as_float(rb[i][0]), __uint_as_float(rb[i][1])};
+          if (two_parts) {
+            set = set && rc[i][0] != 0u && rc[i][1] != 0u && rd[i][0] != 0u && rd[i][1] != 0u;
+            v[0] += __uint_as_float(rc[i][0]);
+            v[1] += __uint_as_float(rc[i][1]);
+            v[2] += __uint_as_float(rd[i][0]);
+            v[3] += __uint_as_float(rd[i][1]);
+          }
+          there = there && (set || col < 0);
+          if (spins >= kLinkSpins) v[0] = __uint_as_float(kLinkNan);
+          const uint32_t h0 = pack_bf16x2(v[0], v[2]), h1 = pack_bf16x2(v[1], v[3]);
+          const uint32_t l0 =
+              pack_bf16x2(v[0] - bf16_to_f32(h0 & 0xffffu), v[2] - bf16_to_f32(h0 >> 16));
+          const uint32_t l1 =
+              pack_bf16x2(v[1] - bf16_to_f32(h1 & 0xffffu), v[3] - bf16_to_f32(h1 >> 16));
+          const int slot = ((R.cw + R.wpt * i) * kGroupWords + (rem >> 1)) * kSlot;
+          uint8_t *dst = (col >= 0 ? xs + slot : junk) + 64 * (rem & 1) + 8 * qq;
+          *reinterpret_cast<uint2 *>(dst) = make_uint2(h0, h1);
+          *reinterpret_cast<uint2 *>(dst + 32) = make_uint2(l0, l1);
+        }
+        if (__all(there) || spins >= kLinkSpins) break;
+      }
+    } else if (kHiLoCols && !shared && b == 1) {
       // One batch row: the 64 lanes share a group's 16 units, a quarter
       // unit each (columns c, c+1 and their partners c+16, c+17), so the
       // conversion costs a quarter of the per-lane instructions of whole
@@ -449,6 +606,7 @@ __device__ __forceinline__ void stage_body(
         }
       }
       if (c0 == 0) load_signs();
+      if (kLink == kLinkOut && tid == 0) ticket = link_ticket(link, link_grid);
 #pragma unroll
       for (int i = 0; i < kMaxGroups; ++i) {
         if (c0 + i >= R.my_groups) break;  // uniform
@@ -482,11 +640,12 @@ __device__ __forceinline__ void stage_body(
       }
     } else {
       load_signs();
+      if (kLink == kLinkOut && tid == 0) ticket = link_ticket(link, link_grid);
       // pass stride and this thread's first unit
       const int stride = shared ? 2 * kThreads : 128;
       const int first = shared ? tid : lane;
       const int wave_first = shared ? 64 * wave : 0;
-#pragma unroll
+#pragma unroll(kLoop ? 1 : kStageIters)
       for (int it = 0; it < (kLoop ? 1 << 20 : kStageIters); ++it) {
         const int base = it * stride;
         if (base >= nunits) break;  // uniform
@@ -549,8 +708,9 @@ __device__ __forceinline__ void stage_body(
   const int nout = rows_wg * b;
   // uniform, <= kMaxOutPerThread (one tile: 16 b <= 256 outputs)
   const int nk_out = kMulti ? (nout + kThreads - 1) / kThreads : 1;
-  uint32_t rscale_bits[kMaxOutPerThread];
-  if (pre) {
+  if constexpr (kLink == kLinkIn) {
+    // loaded ahead
+  } else if (pre) {
 #pragma unroll
     for (int k = 0; k < kMaxOutPerThread; ++k) rscale_bits[k] = pre->rs[k];
   } else {
@@ -658,7 +818,10 @@ __device__ __forceinline__ void stage_body(
   if (red_off == 0) __syncthreads();  // uniform
   reinterpret_cast<float4 *>(lds + red_off)[wave * kRedLanes + lane + (lane >> 4)] =
       make_float4(tot[0], tot[1], tot[2], tot[3]);
+  if (kLink == kLinkOut && tid == 0) s_link = ticket;
   __syncthreads();
+  uint32_t *link_out = nullptr;
+  if constexpr (kLink == kLinkOut) link_out = link_buffer(link, s_link);
   const float *redf = reinterpret_cast<const float *>(lds + red_off);
   float sum[kMaxOutPerThread];
 #pragma unroll
@@ -738,7 +901,11 @@ __device__ __forceinline__ void stage_body(
     if (o < nout && orow < rows) {
       size_t oi = (size_t)(o >> rows_log2) * rows + orow;
       if (mode == kModePartial) oi += (size_t)slab * b * rows;
-      if constexpr (kCoherent) {
+      if constexpr (kLink == kLinkOut) {
+        // +0 would read as not there; -0 adds the same
+        const uint32_t bits = __float_as_uint(v);
+        store_device_word(link_out + oi, bits == 0u ? 0x80000000u : bits);
+      } else if constexpr (kCoherent) {
         if constexpr (kOutY)
           store_device_u16(static_cast<uint16_t *>(out) + oi, f32_to_bf16(v));
         else
@@ -765,6 +932,30 @@ __global__ __launch_bounds__(kThreads) void gemv_stage_kernel(
   stage_body<kInX, kOutY, kHiLoCols, kMulti>(M, in, s_in, row_scale, rows, wpr, slab_words, b,
                                              rt_log2, nslabs, mode, in_parts, out, part, cnt,
                                              (int)blockIdx.x, (int)blockIdx.y, red_off);
+}
+
+// Both stages of one layer with one row tile per workgroup: workgroups below G1
+// the first product (groups1 row groups, then the second column half), the
+// others the second, through the link.  At 1024x4096, b = 1, the first
+// product's last value is stored 2.7 us after the first workgroup starts and
+// the call ends at 4.5, with one boundary of 1.05 us beside it.
+__global__ __launch_bounds__(kThreads, 4) void gemv_fused_kernel(
+    const uint32_t *__restrict__ Bv, const void *__restrict__ x,
+    const uint16_t *__restrict__ s_in, const uint32_t *__restrict__ Bu, int r, int wpr1, int m,
+    int wpr2, int G1, int slab1, int b, int groups1, uint32_t *hdr,
+    const uint16_t *__restrict__ s_mid, const uint16_t *__restrict__ s_out, int nslabs1,
+    int slab2, int red1, int red2, int G, uint16_t *__restrict__ y) {
+  const int id = (int)blockIdx.x;
+  if (id < G1) {
+    const int slab = id >= groups1 ? 1 : 0;
+    stage_body<true, false, true, false, false, false, kLinkOut>(
+        Bv, x, s_in, s_mid, r, wpr1, slab1, b, 0, nslabs1, nslabs1 > 1 ? kModePartial : kModeFinal,
+        1, nullptr, nullptr, nullptr, id - slab * groups1, slab, red1, nullptr, hdr, G);
+  } else {
+    stage_body<false, true, true, false, false, false, kLinkIn>(
+        Bu, nullptr, nullptr, s_out, m, wpr2, slab2, b, 0, 1, kModeFinal, nslabs1, y, nullptr,
+        nullptr, id - G1, 0, red2, nullptr, hdr, G, id - G1, G - G1);
+  }
 }
 
 // One stage of several layers that share the input width (the segments):
@@ -946,24 +1137,31 @@ struct StageArgs {
   uint32_t *cnt;
 };
 
+// The LDS of a stage launch: the staged input and the cross-wave sums.  With
+// one row tile per workgroup the sums get their own region past the staged
+// input when it fits (one barrier instead of two): *red_off > 0.
+size_t stage_lds(const StagePlan &p, int64_t b, int wpr, int *red_off) {
+  const int sw = p.slab_words < wpr ? p.slab_words : wpr;
+  size_t lds = lds_bytes_for(b, sw);
+  *red_off = 0;
+  if (p.rt_log2 == 0) {
+    const size_t stage = (lds_stage_bytes(b, sw) + 15) & ~(size_t)15;
+    if (stage + kRedBytes <= (size_t)kLdsBudget) {
+      *red_off = (int)stage;
+      lds = stage + kRedBytes;
+    }
+  }
+  return lds;
+}
+
 template <bool kInX, bool kOutY>
 hipError_t launch_stage(const StageArgs &a, const StagePlan &p, hipStream_t s) {
   const int rows_wg = kTileRows << p.rt_log2;
   if ((int64_t)rows_wg * a.b > (int64_t)kThreads * kMaxOutPerThread) return hipErrorInvalidValue;
   dim3 grid((unsigned)((a.rows + rows_wg - 1) / rows_wg), (unsigned)p.nslabs);
   const bool multi = p.rt_log2 > 0;
-  size_t lds = lds_bytes_for(a.b, p.slab_words < a.wpr ? p.slab_words : a.wpr);
-  // One row tile per workgroup: the cross-wave sums get their own LDS region
-  // past the staged input when it fits (one barrier instead of two).
   int red_off = 0;
-  if (!multi) {
-    const size_t stage = (lds_stage_bytes(a.b, p.slab_words < a.wpr ? p.slab_words : a.wpr) + 15) &
-                         ~(size_t)15;
-    if (stage + kRedBytes <= (size_t)kLdsBudget) {
-      red_off = (int)stage;
-      lds = stage + kRedBytes;
-    }
-  }
+  const size_t lds = stage_lds(p, a.b, a.wpr, &red_off);
   auto go = [&](auto kernel) -> hipError_t {
     if (!launch_fits(reinterpret_cast<const void *>(kernel), lds)) return hipErrorInvalidValue;
     kernel<<<grid, kThreads, lds, s>>>(a.M, a.in, a.s_in, a.row_scale, a.rows, a.wpr,
@@ -976,6 +1174,41 @@ hipError_t launch_stage(const StageArgs &a, const StagePlan &p, hipStream_t s) {
                  : go(gemv_stage_kernel<kInX, kOutY, true, false>);
   return multi ? go(gemv_stage_kernel<kInX, kOutY, false, true>)
                : go(gemv_stage_kernel<kInX, kOutY, false, false>);
+}
+
+// Whether a layer's two stages run as one launch: one row tile per workgroup in
+// both, no last-slab reduction, the intermediate fits a link buffer, every
+// ticket word gets a workgroup, and few enough workgroups (five for every four
+// units) that the waiting ones share few units with the first stage's.
+// Measured at b = 1, one launch against two: 1024^2 5.7 / 6.1 us, 1024x4096 5.9
+// / 6.7, 2048^2 5.9 / 6.3, 2048x4096 (296 workgroups) 6.3 / 7.1; with more
+// workgroups the gain shrinks (4096x2048, 424: 6.5 / 6.7; 4096^2, 508: 7.0 /
+// 7.3 in a pool of layers, but 0.6 us slower inside a decoder step) and turns
+// (8192^2, 768: 11.7 / 11.0).  Batches above 1 gain nothing (3584^2 at b = 2:
+// 8.6 / 8.3): the waiting workgroups poll and convert b times as many words.
+bool fused_ok(const StagePlan &p1, const StagePlan &p2, int64_t m, int64_t r, int64_t b, int cus) {
+  const int64_t parts = p1.mode == kModePartial ? p1.nslabs : 1;
+  const int64_t g = (r + kTileRows - 1) / kTileRows * parts + (m + kTileRows - 1) / kTileRows;
+  return b == 1 && p1.rt_log2 == 0 && p2.rt_log2 == 0 && p1.mode != kModeLastSlab &&
+         p2.mode == kModeFinal && parts <= 2 && parts * b * r <= kLinkWords && g >= kLinkSlots &&
+         4 * g <= 5 * cus;
+}
+
+hipError_t launch_fused(const StageArgs &a1, const StageArgs &a2, const StagePlan &p1,
+                        const StagePlan &p2, uint32_t *hdr, hipStream_t s) {
+  const int groups1 = (a1.rows + kTileRows - 1) / kTileRows;
+  const int parts = p1.mode == kModePartial ? p1.nslabs : 1;
+  const int G1 = groups1 * parts, G = G1 + (a2.rows + kTileRows - 1) / kTileRows;
+  int red1 = 0, red2 = 0;
+  const size_t l1 = stage_lds(p1, a1.b, a1.wpr, &red1), l2 = stage_lds(p2, a2.b, a2.wpr, &red2);
+  const size_t lds = l1 > l2 ? l1 : l2;
+  if (!launch_fits(reinterpret_cast<const void *>(gemv_fused_kernel), lds))
+    return hipErrorInvalidValue;
+  gemv_fused_kernel<<<G, kThreads, lds, s>>>(
+      a1.M, a1.in, a1.s_in, a2.M, a1.rows, a1.wpr, a2.rows, a2.wpr, G1, p1.slab_words, a1.b,
+      groups1, hdr, a1.row_scale, a2.row_scale, parts, p2.slab_words, red1, red2, G,
+      static_cast<uint16_t *>(a2.out));
+  return hipGetLastError();
 }
 
 template <bool kInX, bool kOutY>
@@ -1139,19 +1372,21 @@ hipError_t launch_gemv(int64_t m, int64_t n, int64_t r, const uint32_t *Bu,
                        const uint32_t *Bv, const uint16_t *s_out,
                        const uint16_t *s_mid, const uint16_t *s_in,
                        const uint16_t *x, int64_t b, uint16_t *y, void *ws,
-                       hipStream_t s) {
+                       hipStream_t s, bool link) {
   const WsLayout L = ws_layout(m, n, r, b, device_cus());
   uint8_t *base = static_cast<uint8_t *>(ws);
   float *t = reinterpret_cast<float *>(base + L.t);
   const StageArgs s1{Bv, x, s_in, s_mid, (int)r, (int)(n / 32), (int)b, 1, t,
                      reinterpret_cast<float *>(base + L.part1),
                      reinterpret_cast<uint32_t *>(base + L.cnt1)};
-  hipError_t e = launch_stage<true, false>(s1, L.p1, s);
-  if (e != hipSuccess) return e;
   const int tparts = L.p1.mode == kModePartial ? L.p1.nslabs : 1;
   const StageArgs s2{Bu, t, nullptr, s_out, (int)m, (int)(r / 32), (int)b, tparts, y,
                      reinterpret_cast<float *>(base + L.part2),
                      reinterpret_cast<uint32_t *>(base + L.cnt2)};
+  if (link && fused_ok(L.p1, L.p2, m, r, b, device_cus()))
+    return launch_fused(s1, s2, L.p1, L.p2, reinterpret_cast<uint32_t *>(base), s);
+  const hipError_t e = launch_stage<true, false>(s1, L.p1, s);
+  if (e != hipSuccess) return e;
   return launch_stage<false, true>(s2, L.p2, s);
 }
 
@@ -1385,20 +1620,6 @@ __global__ __launch_bounds__(kStreamThreads, 2) void stream_kernel(const uint8_t
     store_device_u32(sync + kSyncEpoch, epoch + (uint32_t)nphases);
 }
 
-size_t seg_lds_bytes(const StagePlan &p, int64_t b, int wpr, int *red_off) {
-  const int sw = p.slab_words < wpr ? p.slab_words : wpr;
-  size_t lds = lds_bytes_for(b, sw);
-  *red_off = 0;
-  if (p.rt_log2 == 0) {
-    const size_t stage = (lds_stage_bytes(b, sw) + 15) & ~(size_t)15;
-    if (stage + kRedBytes <= (size_t)kLdsBudget) {
-      *red_off = (int)stage;
-      lds = stage + kRedBytes;
-    }
-  }
-  return lds;
-}
-
 struct PendingSeg {
   int item, kind;
   StagePlan p;
@@ -1588,7 +1809,7 @@ void stream_plan_impl(const af1_stream_item *items, int count, int64_t b, void *
       task += g.groups * g.nslabs;
       g.task_end = task;
       int red_off = 0;
-      const size_t lds = seg_lds_bytes(sgm.p, b, g.wpr, &red_off);
+      const size_t lds = stage_lds(sgm.p, b, g.wpr, &red_off);
       g.red_off = red_off;
       if (lds > lds_max) lds_max = lds;
       // the item's t in the workspace

@@ -25,11 +25,13 @@ hipError_t launch_transpose(const uint32_t *src, int64_t rows, int64_t cols, uin
                             hipStream_t s);
 
 size_t gemv_workspace_bytes(int64_t m, int64_t n, int64_t r, int64_t b);
+// link: the call may run as one launch whose stages meet in the workspace
+// header (which then has to be as af1_linear_gemv asks).
 hipError_t launch_gemv(int64_t m, int64_t n, int64_t r, const uint32_t *Bu,
                        const uint32_t *Bv, const uint16_t *s_out,
                        const uint16_t *s_mid, const uint16_t *s_in,
                        const uint16_t *x, int64_t b, uint16_t *y, void *ws,
-                       hipStream_t s);
+                       hipStream_t s, bool link = true);
 
 // Zero the arrival counters that launch_gemv uses for this shape and batch
 // (none when no stage splits its columns); a fill kernel, no memset node.

@@ -59,7 +59,7 @@ af1_status af1_linear_gemv_noalloc(const af1_factorized_linear *L, const uint16_
   if (af1::launch_gemv_clear_counters(L->m, L->n, L->r, b, ws, s) != hipSuccess)
     return AF1_ERR_HIP;
   return hip_status(af1::launch_gemv(L->m, L->n, L->r, L->Bu, L->Bv, L->s_out, L->s_mid,
-                                     L->s_in, x, b, y, ws, s));
+                                     L->s_in, x, b, y, ws, s, false));
 }
 
 }  // extern "C"
