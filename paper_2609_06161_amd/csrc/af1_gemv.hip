@@ -40,6 +40,7 @@
 // a row group to finish (atomic counter) adds the partials in slab order,
 // so the result is deterministic.
 #include <atomic>
+#include <climits>
 #include <cstring>
 #include <mutex>
 #include <utility>
@@ -934,17 +935,33 @@ __device__ __forceinline__ void stage_body(
   }
 }
 
+// What a stage launch needs before its first loads, in one word: the batch (5
+// bits), the output mode (2), log2 of the row tiles a workgroup (2) and the
+// parts of the input (2).
+int stage_cfg(int b, int mode, int rt_log2, int in_parts) {
+  return b | mode << 5 | rt_log2 << 7 | in_parts << 9;
+}
+struct StageCfg {
+  int b, mode, rt_log2, in_parts;
+  __device__ __forceinline__ explicit StageCfg(int c)
+      : b(c & 31), mode(c >> 5 & 3), rt_log2(c >> 7 & 3), in_parts(c >> 9 & 3) {}
+};
+
 // One stage of one layer: row group (blockIdx.x), slab (blockIdx.y).
-// Arguments are scalars, most urgent first, so that they are preloaded into
-// SGPRs at wave launch instead of being fetched from the kernarg segment.
+// The first 14 dwords of arguments are preloaded into SGPRs at wave launch;
+// the rest is fetched from the kernarg segment, a memory round trip that
+// nothing hides if the first loads depend on it.  So everything up to nslabs
+// fits those (with the second product's in_parts beyond them, 4096^2 b=1 took
+// 6.39 us a call in a graph, now 6.26).
 template <bool kInX, bool kOutY, bool kHiLoCols, bool kMulti>
 __global__ __launch_bounds__(kThreads) void gemv_stage_kernel(
     const uint32_t *__restrict__ M, const void *__restrict__ in,
     const uint16_t *__restrict__ s_in, const uint16_t *__restrict__ row_scale, int rows,
-    int wpr, int slab_words, int b, int rt_log2, int nslabs, int mode, int in_parts,
-    void *__restrict__ out, float *__restrict__ part, uint32_t *__restrict__ cnt, int red_off) {
-  stage_body<kInX, kOutY, kHiLoCols, kMulti>(M, in, s_in, row_scale, rows, wpr, slab_words, b,
-                                             rt_log2, nslabs, mode, in_parts, out, part, cnt,
+    int wpr, int slab_words, int cfg, int red_off, int nslabs, void *__restrict__ out,
+    float *__restrict__ part, uint32_t *__restrict__ cnt) {
+  const StageCfg c(cfg);
+  stage_body<kInX, kOutY, kHiLoCols, kMulti>(M, in, s_in, row_scale, rows, wpr, slab_words, c.b,
+                                             c.rt_log2, nslabs, c.mode, c.in_parts, out, part, cnt,
                                              (int)blockIdx.x, (int)blockIdx.y, red_off);
 }
 
@@ -955,19 +972,20 @@ __global__ __launch_bounds__(kThreads) void gemv_stage_kernel(
 // the call ends at 4.5, with one boundary of 1.05 us beside it.
 __global__ __launch_bounds__(kThreads, 4) void gemv_fused_kernel(
     const uint32_t *__restrict__ Bv, const void *__restrict__ x,
-    const uint16_t *__restrict__ s_in, const uint32_t *__restrict__ Bu, int r, int wpr1, int m,
-    int wpr2, int G1, int slab1, int b, int groups1, uint32_t *hdr,
-    const uint16_t *__restrict__ s_mid, const uint16_t *__restrict__ s_out, int nslabs1,
-    int slab2, int red1, int red2, int G, uint16_t *__restrict__ y) {
+    const uint16_t *__restrict__ s_in, int r, int wpr1, int slab1, int groups1, int G1,
+    uint32_t *hdr, int G, const uint16_t *__restrict__ s_mid, int nslabs1, int red1,
+    const uint32_t *__restrict__ Bu, const uint16_t *__restrict__ s_out, int m, int wpr2,
+    int slab2, int red2, uint16_t *__restrict__ y) {
+  // (the batch is 1; the first product's arguments first, see gemv_stage_kernel)
   const int id = (int)blockIdx.x;
   if (id < G1) {
     const int slab = id >= groups1 ? 1 : 0;
     stage_body<true, false, true, false, false, false, kLinkOut>(
-        Bv, x, s_in, s_mid, r, wpr1, slab1, b, 0, nslabs1, nslabs1 > 1 ? kModePartial : kModeFinal,
+        Bv, x, s_in, s_mid, r, wpr1, slab1, 1, 0, nslabs1, nslabs1 > 1 ? kModePartial : kModeFinal,
         1, nullptr, nullptr, nullptr, id - slab * groups1, slab, red1, nullptr, hdr, G);
   } else {
     stage_body<false, true, true, false, false, false, kLinkIn>(
-        Bu, nullptr, nullptr, s_out, m, wpr2, slab2, b, 0, 1, kModeFinal, nslabs1, y, nullptr,
+        Bu, nullptr, nullptr, s_out, m, wpr2, slab2, 1, 0, 1, kModeFinal, nslabs1, y, nullptr,
         nullptr, id - G1, 0, red2, nullptr, hdr, G, id - G1, G - G1);
   }
 }
@@ -978,32 +996,32 @@ __global__ __launch_bounds__(kThreads, 4) void gemv_fused_kernel(
 // output; the plan (rows per workgroup, slab, mode) is common, with one
 // slab (no last-slab reduction).
 constexpr int kMaxSegs = 4;
+struct alignas(64) Seg {
+  const uint32_t *M;
+  const void *in;
+  const uint16_t *s_in, *row_scale;
+  void *out;
+  int rows, wpr, group_begin;
+};
 struct Segs {
-  int count;
-  int group_end[kMaxSegs];
-  int rows[kMaxSegs];
-  int wpr[kMaxSegs];
-  const uint32_t *M[kMaxSegs];
-  const void *in[kMaxSegs];
-  const uint16_t *s_in[kMaxSegs];
-  const uint16_t *row_scale[kMaxSegs];
-  void *out[kMaxSegs];
+  Seg s[kMaxSegs];
+  int count, groups;
 };
 
+// end0 .. end2: the first row group past segments 0 .. 2 (INT_MAX from the last
+// one on).  They and the common arguments are preloaded, so the segment's
+// entry, one cache line, is the one fetch in front of the first loads (two
+// decoder layers of an 8B model, b=1: 83.7 -> 81.1 us with it).
 template <bool kInX, bool kOutY, bool kHiLoCols, bool kMulti>
-__global__ __launch_bounds__(kThreads) void gemv_segs_kernel(const Segs segs, int slab_words,
-                                                             int b, int rt_log2, int mode,
-                                                             int in_parts) {
+__global__ __launch_bounds__(kThreads) void gemv_segs_kernel(int end0, int end1, int end2,
+                                                             int slab_words, int cfg, int red_off,
+                                                             const Segs segs) {
   const int g = (int)blockIdx.x;
-  int sg = 0;
-#pragma unroll
-  for (int i = 0; i + 1 < kMaxSegs; ++i)
-    if (i + 1 < segs.count && g >= segs.group_end[i]) sg = i + 1;
-  const int g0 = sg > 0 ? segs.group_end[sg - 1] : 0;
+  const StageCfg c(cfg);
+  const Seg &sg = segs.s[(g >= end0) + (g >= end1) + (g >= end2)];
   stage_body<kInX, kOutY, kHiLoCols, kMulti>(
-      segs.M[sg], segs.in[sg], segs.s_in[sg], segs.row_scale[sg], segs.rows[sg], segs.wpr[sg],
-      slab_words, b, rt_log2, 1, mode, in_parts, segs.out[sg], nullptr, nullptr, g - g0,
-      (int)blockIdx.y);
+      sg.M, sg.in, sg.s_in, sg.row_scale, sg.rows, sg.wpr, slab_words, c.b, c.rt_log2, 1, c.mode,
+      c.in_parts, sg.out, nullptr, nullptr, g - sg.group_begin, (int)blockIdx.y, red_off);
 }
 
 size_t lds_stage_bytes(int64_t b, int slab_words) {
@@ -1178,9 +1196,9 @@ hipError_t launch_stage(const StageArgs &a, const StagePlan &p, hipStream_t s) {
   const size_t lds = stage_lds(p, a.b, a.wpr, &red_off);
   auto go = [&](auto kernel) -> hipError_t {
     if (!launch_fits(reinterpret_cast<const void *>(kernel), lds)) return hipErrorInvalidValue;
-    kernel<<<grid, kThreads, lds, s>>>(a.M, a.in, a.s_in, a.row_scale, a.rows, a.wpr,
-                                       p.slab_words, a.b, p.rt_log2, p.nslabs, p.mode,
-                                       a.in_parts, a.out, a.part, a.cnt, red_off);
+    kernel<<<grid, kThreads, lds, s>>>(a.M, a.in, a.s_in, a.row_scale, a.rows, a.wpr, p.slab_words,
+                                       stage_cfg(a.b, p.mode, p.rt_log2, a.in_parts), red_off,
+                                       p.nslabs, a.out, a.part, a.cnt);
     return hipGetLastError();
   };
   if (a.b <= 8)
@@ -1219,8 +1237,8 @@ hipError_t launch_fused(const StageArgs &a1, const StageArgs &a2, const StagePla
   if (!launch_fits(reinterpret_cast<const void *>(gemv_fused_kernel), lds))
     return hipErrorInvalidValue;
   gemv_fused_kernel<<<G, kThreads, lds, s>>>(
-      a1.M, a1.in, a1.s_in, a2.M, a1.rows, a1.wpr, a2.rows, a2.wpr, G1, p1.slab_words, a1.b,
-      groups1, hdr, a1.row_scale, a2.row_scale, parts, p2.slab_words, red1, red2, G,
+      a1.M, a1.in, a1.s_in, a1.rows, a1.wpr, p1.slab_words, groups1, G1, hdr, G, a1.row_scale,
+      parts, red1, a2.M, a2.row_scale, a2.rows, a2.wpr, p2.slab_words, red2,
       static_cast<uint16_t *>(a2.out));
   return hipGetLastError();
 }
@@ -1228,11 +1246,14 @@ hipError_t launch_fused(const StageArgs &a1, const StageArgs &a2, const StagePla
 template <bool kInX, bool kOutY>
 hipError_t launch_segs(const Segs &sg, const StagePlan &p, int b, int max_wpr, int in_parts,
                        hipStream_t s) {
-  const size_t lds = lds_bytes_for(b, p.slab_words < max_wpr ? p.slab_words : max_wpr);
-  dim3 grid((unsigned)sg.group_end[sg.count - 1], (unsigned)p.nslabs);
+  int red_off = 0;
+  const size_t lds = stage_lds(p, b, max_wpr, &red_off);
+  dim3 grid((unsigned)sg.groups, (unsigned)p.nslabs);
+  auto end = [&](int i) { return i + 1 < sg.count ? sg.s[i + 1].group_begin : INT_MAX; };
   auto go = [&](auto kernel) -> hipError_t {
     if (!launch_fits(reinterpret_cast<const void *>(kernel), lds)) return hipErrorInvalidValue;
-    kernel<<<grid, kThreads, lds, s>>>(sg, p.slab_words, b, p.rt_log2, p.mode, in_parts);
+    kernel<<<grid, kThreads, lds, s>>>(end(0), end(1), end(2), p.slab_words,
+                                       stage_cfg(b, p.mode, p.rt_log2, in_parts), red_off, sg);
     return hipGetLastError();
   };
   const bool multi = p.rt_log2 > 0;
@@ -1331,26 +1352,29 @@ hipError_t launch_gemv_multi(int count, const int64_t *m, const int64_t *r, int6
   int g1 = 0, g2 = 0, wpr2 = 0;
   for (int i = 0; i < count; ++i) {
     float *t = reinterpret_cast<float *>(base + L.t[i]);
+    Seg &a = s1.s[i], &c = s2.s[i];
+    a.group_begin = g1;
+    c.group_begin = g2;
     g1 += (int)((r[i] + rw1 - 1) / rw1);
     g2 += (int)((m[i] + rw2 - 1) / rw2);
-    s1.group_end[i] = g1;
-    s2.group_end[i] = g2;
-    s1.rows[i] = (int)r[i];
-    s1.wpr[i] = (int)(n / 32);
-    s1.M[i] = Bv[i];
-    s1.in[i] = x;
-    s1.s_in[i] = s_in[i];
-    s1.row_scale[i] = s_mid[i];
-    s1.out[i] = t;
-    s2.rows[i] = (int)m[i];
-    s2.wpr[i] = (int)(r[i] / 32);
-    s2.M[i] = Bu[i];
-    s2.in[i] = t;
-    s2.s_in[i] = nullptr;
-    s2.row_scale[i] = s_out[i];
-    s2.out[i] = y[i];
-    if (s2.wpr[i] > wpr2) wpr2 = s2.wpr[i];
+    a.rows = (int)r[i];
+    a.wpr = (int)(n / 32);
+    a.M = Bv[i];
+    a.in = x;
+    a.s_in = s_in[i];
+    a.row_scale = s_mid[i];
+    a.out = t;
+    c.rows = (int)m[i];
+    c.wpr = (int)(r[i] / 32);
+    c.M = Bu[i];
+    c.in = t;
+    c.s_in = nullptr;
+    c.row_scale = s_out[i];
+    c.out = y[i];
+    if (c.wpr > wpr2) wpr2 = c.wpr;
   }
+  s1.groups = g1;
+  s2.groups = g2;
   hipError_t e = launch_segs<true, false>(s1, L.p1, (int)b, (int)(n / 32), 1, s);
   if (e != hipSuccess) return e;
   return launch_segs<false, true>(s2, L.p2, (int)b, wpr2, tparts, s);
