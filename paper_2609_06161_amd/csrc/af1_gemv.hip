@@ -144,11 +144,20 @@ __device__ __forceinline__ void static_for_until(int n, F &&f) {
   }
 }
 
-// Buffer resource over [base, base + bytes): loads at offsets beyond `bytes`
-// return zero instead of faulting.  Word 3 selects raw 32-bit dword access.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc(const void *base, int64_t bytes) {
-  const int n = bytes > 0x7fffffff ? 0x7fffffff : (bytes < 0 ? 0 : (int)bytes);
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, n, 0x00020000);
+// Buffer resource over [base, base + bytes), bytes >= 0: loads at offsets
+// beyond `bytes` return zero instead of faulting.  Word 3 selects raw 32-bit
+// dword access.  (With dimensions up to 2^20 and 16 batch rows everything but
+// the partial sums is far below 2^31 bytes; a 64-bit size costs a chain of
+// vector compares and selects in front of the first loads.)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc(const void *base, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, bytes, 0x00020000);
+}
+static_assert((int64_t)AF1_MAX_DIM * AF1_GEMV_MAX_BATCH * 4 * 2 < 0x7fffffff, "resource sizes");
+
+// The sign words of a 16-row tile: `rows` rows are left from the tile's first
+// one, M points there.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const uint32_t *M, int rows, int wpr) {
+  return buffer_rsrc(M, min(max(rows, 0), 16) * wpr * 4);
 }
 
 // Two fp32 -> packed bf16 (round to nearest even), one instruction on gfx950.
@@ -375,7 +384,7 @@ __device__ __forceinline__ void load_row_scales(uint32_t (&rs)[kMaxOutPerThread]
   const int rows_wg = 16 << rt_log2;
   const int row_wg0 = group * rows_wg;
   const int nout = rows_wg * b;
-  const __amdgpu_buffer_rsrc_t rres = buffer_rsrc(row_scale, (int64_t)rows * 2);
+  const __amdgpu_buffer_rsrc_t rres = buffer_rsrc(row_scale, rows * 2);
 #pragma unroll
   for (int k = 0; k < kMaxOutPerThread; ++k) {
     // the first load is unconditional (and so is its use below): a load
@@ -405,8 +414,7 @@ __device__ __forceinline__ void stage_signs(SignRegs &sg, const uint32_t *__rest
   const int nout = (16 << rt_log2) * b;
   load_row_scales(sg.rs, row_scale, rows, group, rt_log2, b,
                   rt_log2 > 0 ? (nout + kThreads - 1) / kThreads : 1);
-  const int64_t left = (int64_t)(rows - R.row0) * wpr * 4;
-  const __amdgpu_buffer_rsrc_t mres = buffer_rsrc(M + (size_t)R.row0 * wpr, left);
+  const __amdgpu_buffer_rsrc_t mres = tile_rsrc(M + (size_t)R.row0 * wpr, rows - R.row0, wpr);
 #pragma unroll
   for (int i = 0; i < kMaxGroups; ++i) sg.wv[i] = u32x2{0u, 0u};
   static_for_until<kMaxGroups>(R.my_groups, [&](auto I) {  // uniform
@@ -464,8 +472,7 @@ __device__ __forceinline__ void stage_body(
   u32x2 wv[kMaxGroups];
   // sign words of groups c0 .. c0 + kMaxGroups - 1 into dst
   auto load_chunk = [&](u32x2 (&dst)[kMaxGroups], int c0) {
-    const int64_t left = (int64_t)(rows - R.row0) * wpr * 4;
-    const __amdgpu_buffer_rsrc_t mres = buffer_rsrc(M + (size_t)R.row0 * wpr, left);
+      const __amdgpu_buffer_rsrc_t mres = tile_rsrc(M + (size_t)R.row0 * wpr, rows - R.row0, wpr);
 #pragma unroll
     for (int i = 0; i < kMaxGroups; ++i) dst[i] = u32x2{0u, 0u};
     static_for_until<kMaxGroups>(R.my_groups - c0, [&](auto I) {  // uniform
@@ -523,11 +530,11 @@ __device__ __forceinline__ void stage_body(
     const int per_group = b * kGroupWords * 2;  // units of one group
     const int nunits = shared ? b * 2 * w_count : R.my_groups * per_group;
     const int span = shared ? 2 * w_count : per_group;
-    const float inv_span = 1.0f / (float)span;
+    const float inv_span = __builtin_amdgcn_rcpf((float)span);  // corrected below
     const int part_elems = b * (int)K;  // stride between partial input arrays
     const __amdgpu_buffer_rsrc_t xres =
-        buffer_rsrc(in, (int64_t)b * K * (kInX ? 2 : 4) * (kInX ? 1 : in_parts));
-    const __amdgpu_buffer_rsrc_t sres = buffer_rsrc(s_in, kInX ? (int64_t)K * 2 : 0);
+        buffer_rsrc(in, b * wpr * (kInX ? 64 : 128) * (kInX ? 1 : in_parts));
+    const __amdgpu_buffer_rsrc_t sres = buffer_rsrc(s_in, kInX ? wpr * 64 : 0);
     const bool two_parts = !kInX && in_parts > 1;
     const int bstride = row_stride(w_count);
     uint8_t *junk = xs + (size_t)b * bstride + (tid & 15) * kSlot;
@@ -761,12 +768,18 @@ __device__ __forceinline__ void stage_body(
     const int hl = kHiLoCols ? 0 : (k >> 2), t = k & 3;
     return 16 * (4 * (t >> 1) + 2 * hl + (t & 1));
   };
+  // this lane's first word, and its slot
+  const int b_word0 = R.cw * kGroupWords + 2 * q;
+  const int b_off0 = kSlot + beta * row_stride(w_count) + b_word0 * kSlot + 32 * hl_col;
   // the products of the wave's groups c0 .. c0 + kMaxGroups - 1 (sign words w)
   auto products = [&](const u32x2 (&w)[kMaxGroups], int c0, int nsteps) {
+    // (a scalar step and a select a read: as one expression of the word it
+    // became a multiply under its own exec mask, and two 8B decoder layers at
+    // b=1 took 85.1 us instead of 81.9)
     auto b_ptr = [&](int st) -> const uint8_t * {
-      const int wl = (R.cw + R.wpt * (c0 + (st >> 1))) * kGroupWords + 2 * q + (st & 1);
-      return wl < w_count ? xs + (size_t)beta * row_stride(w_count) + wl * kSlot + 32 * hl_col
-                          : lds;
+      const int step = R.wpt * kGroupWords * (c0 + (st >> 1)) + (st & 1);
+      const int off = b_off0 + step * kSlot;
+      return lds + (b_word0 + step < w_count ? off : 0);
     };
     uint4 bop[2][kReads];
 #pragma unroll
@@ -882,7 +895,7 @@ __device__ __forceinline__ void stage_body(
     if (!s_last) return;
     // Device-scope loads of every slab's partial, issued before any is
     // added (the slab count is small: at most kMaxSlabsLoaded per pass).
-    const __amdgpu_buffer_rsrc_t pres = buffer_rsrc(part, (int64_t)nslabs * b * rows * 4);
+    const __amdgpu_buffer_rsrc_t pres = buffer_rsrc(part, (int)min((int64_t)nslabs * b * rows * 4, (int64_t)0x7fffffff));
 #pragma unroll
     for (int k = 0; k < kMaxOutPerThread; ++k) {
       if (k >= nk_out) break;
@@ -1522,7 +1535,7 @@ __device__ bool barrier_wait(uint32_t *sync, uint32_t target) {
     const int lane = threadIdx.x;
     const int G = (int)gridDim.x;
     const __amdgpu_buffer_rsrc_t fres = buffer_rsrc(
-        sync + kSyncFlags + (blockIdx.x % kFlagReplicas) * kStreamMaxGrid, (int64_t)G * 4);
+        sync + kSyncFlags + (blockIdx.x % kFlagReplicas) * kStreamMaxGrid, G * 4);
     auto poll = [&](uint32_t (&f)[kStreamMaxGrid / 64]) {
 #pragma unroll
       for (int k = 0; k < kStreamMaxGrid / 64; ++k) {
