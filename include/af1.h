@@ -120,15 +120,16 @@ AF1_API af1_status af1_unpack(const uint32_t *words, int64_t rows, int64_t cols,
  *   x  : device, [b, n] bfloat16.       y : device, [b, m] bfloat16 (written).
  *   b  : 1 .. AF1_GEMV_MAX_BATCH.
  *   ws : device workspace of at least af1_gemv_workspace_bytes(m, n, r, b)
- *        bytes.  Its first 512 KiB are a header of arrival counters at
- *        fixed offsets; the header must be zero-filled before the
- *        workspace's first use, and every call that
- *        completes leaves the counters at zero again, so one workspace
- *        serves any sequence of calls, of any shapes, on one stream.  Calls
+ *        bytes.  Its first 512 KiB are a header of arrival counters, call
+ *        numbers and hand-off words at fixed offsets; the header must be
+ *        zero-filled before the workspace's first use, and every call that
+ *        completes leaves it ready for the next one (not zero), so one
+ *        workspace serves any sequence of GEMV calls, of any shapes, on one
+ *        stream.  Nothing else may write the header in between.  Calls
  *        that may overlap in time need distinct workspaces.  Recovery: a
  *        call that did not run to completion (a launch error reported by
- *        a later call, a killed stream) may leave counters non-zero, after
- *        which results are wrong; zero-fill the header again before reusing
+ *        a later call, a killed stream) may leave the header inconsistent,
+ *        after which results are wrong; zero-fill it again before reusing
  *        such a workspace.
  * Arithmetic: s_in .* x in fp32 (exact), both sign products accumulated in
  * fp32, the rank-r intermediate kept in fp32, scales applied in fp32, y

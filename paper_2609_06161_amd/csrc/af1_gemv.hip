@@ -426,7 +426,7 @@ __device__ __forceinline__ void stage_signs(SignRegs &sg, const uint32_t *__rest
 }
 
 // kLink: the two stages of a layer in one launch (gemv_fused_kernel), the
-// intermediate passed through the link (see LinkHeader): kLinkOut stores it
+// intermediate passed through the link (see kLinkNone above): kLinkOut stores it
 // there, kLinkIn waits for it there.
 // kLoop: a wave may own more than kMaxGroups groups; they are taken in
 // chunks of kMaxGroups, the next chunk's sign words loading while the
@@ -980,9 +980,10 @@ __global__ __launch_bounds__(kThreads) void gemv_stage_kernel(
 
 // Both stages of one layer with one row tile per workgroup: workgroups below G1
 // the first product (groups1 row groups, then the second column half), the
-// others the second, through the link.  At 1024x4096, b = 1, the first
-// product's last value is stored 2.7 us after the first workgroup starts and
-// the call ends at 4.5, with one boundary of 1.05 us beside it.
+// others the second, through the link.  At 1024x4096, b = 1, timestamps taken
+// when the stage bodies were 0.6 us longer had the first product's last value
+// stored 2.7 us after the first workgroup starts and the call end at 4.5, with
+// one boundary of 1.05 us beside it.
 __global__ __launch_bounds__(kThreads, 4) void gemv_fused_kernel(
     const uint32_t *__restrict__ Bv, const void *__restrict__ x,
     const uint16_t *__restrict__ s_in, int r, int wpr1, int slab1, int groups1, int G1,
@@ -1223,20 +1224,21 @@ hipError_t launch_stage(const StageArgs &a, const StagePlan &p, hipStream_t s) {
 
 // Whether a layer's two stages run as one launch: one row tile per workgroup in
 // both, no last-slab reduction, the intermediate fits a link buffer, every
-// ticket word gets a workgroup, and few enough workgroups (five for every four
-// units) that the waiting ones share few units with the first stage's.
-// Measured at b = 1, one launch against two: 1024^2 5.7 / 6.1 us, 1024x4096 5.9
-// / 6.7, 2048^2 5.9 / 6.3, 2048x4096 (296 workgroups) 6.3 / 7.1; with more
-// workgroups the gain shrinks (4096x2048, 424: 6.5 / 6.7; 4096^2, 508: 7.0 /
-// 7.3 in a pool of layers, but 0.6 us slower inside a decoder step) and turns
-// (8192^2, 768: 11.7 / 11.0).  Batches above 1 gain nothing (3584^2 at b = 2:
-// 8.6 / 8.3): the waiting workgroups poll and convert b times as many words.
+// ticket word gets a workgroup, and at most two workgroups a unit, so that all
+// of them are resident at once (where their LDS allows two a unit).  Measured at b = 1 in a graph, one launch
+// against two: 1024^2 4.9 / 5.2 us, 1024x4096 5.05 / 5.6, 2048^2 5.1 / 5.4,
+// 2048x4096 5.4 / 5.9, 3072^2 5.6 / 5.9, 4096^2 (508 workgroups) 5.8 / 6.2; past
+// the line it turns (4096x5120 7.3 / 7.2, 6144x4096 7.7 / 7.6, 8192^2 10.4 /
+// 9.7).  A call from the host is 2.6 us shorter in one launch (4096^2 11.5 ->
+// 8.9).  Batches above 1 gain nothing (3584^2 at b = 2: 8.6 / 8.3 before both
+// forms got shorter): the waiting workgroups poll and convert b times as many
+// words.
 bool fused_ok(const StagePlan &p1, const StagePlan &p2, int64_t m, int64_t r, int64_t b, int cus) {
   const int64_t parts = p1.mode == kModePartial ? p1.nslabs : 1;
   const int64_t g = (r + kTileRows - 1) / kTileRows * parts + (m + kTileRows - 1) / kTileRows;
   return b == 1 && p1.rt_log2 == 0 && p2.rt_log2 == 0 && p1.mode != kModeLastSlab &&
          p2.mode == kModeFinal && parts <= 2 && parts * b * r <= kLinkWords && g >= kLinkSlots &&
-         4 * g <= 5 * cus;
+         g <= 2 * cus;
 }
 
 hipError_t launch_fused(const StageArgs &a1, const StageArgs &a2, const StagePlan &p1,
@@ -1424,7 +1426,8 @@ hipError_t launch_gemv(int64_t m, int64_t n, int64_t r, const uint32_t *Bu,
                        const uint16_t *s_mid, const uint16_t *s_in,
                        const uint16_t *x, int64_t b, uint16_t *y, void *ws,
                        hipStream_t s, bool link) {
-  const WsLayout L = ws_layout(m, n, r, b, device_cus());
+  const int cus = device_cus();
+  const WsLayout L = ws_layout(m, n, r, b, cus);
   uint8_t *base = static_cast<uint8_t *>(ws);
   float *t = reinterpret_cast<float *>(base + L.t);
   const StageArgs s1{Bv, x, s_in, s_mid, (int)r, (int)(n / 32), (int)b, 1, t,
@@ -1434,7 +1437,7 @@ hipError_t launch_gemv(int64_t m, int64_t n, int64_t r, const uint32_t *Bu,
   const StageArgs s2{Bu, t, nullptr, s_out, (int)m, (int)(r / 32), (int)b, tparts, y,
                      reinterpret_cast<float *>(base + L.part2),
                      reinterpret_cast<uint32_t *>(base + L.cnt2)};
-  if (link && fused_ok(L.p1, L.p2, m, r, b, device_cus()))
+  if (link && fused_ok(L.p1, L.p2, m, r, b, cus))
     return launch_fused(s1, s2, L.p1, L.p2, reinterpret_cast<uint32_t *>(base), s);
   const hipError_t e = launch_stage<true, false>(s1, L.p1, s);
   if (e != hipSuccess) return e;
