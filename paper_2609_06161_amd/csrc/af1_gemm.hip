@@ -2310,7 +2310,7 @@ constexpr TokShape kTokShapes[] = {
 };
 
 ContractionPlan plan_contraction(int64_t T, int64_t K, int64_t N, bool allow_split, int cus,
-                                 bool allow_mixed = false) {
+                                 bool allow_mixed = false, bool first = false) {
   ContractionPlan p;
   p.mix_full = p.mix_splits = 0;
   p.bn = BN;
@@ -2350,7 +2350,11 @@ ContractionPlan plan_contraction(int64_t T, int64_t K, int64_t N, bool allow_spl
   double best = contraction_us(p.bm == BM ? kCost128 : kCost64, (double)tiles * p.splits,
                                mixed ? nk : p.split_steps, p.splits, T, N, cus) +
                 (mixed ? kMixedUs : 0.0);
+  // (the forward's first product only where the large tiles leave units idle:
+  // its row sums take a workspace entry a tile, and narrow tiles would enlarge
+  // the workspace of calls that fill the device)
   for (const TokShape &c : kTokShapes) {
+    if (first && tiles >= cus) break;
     const int64_t gx = (N + c.bn - 1) / c.bn, gy = (T + c.bm - 1) / c.bm;
     const int64_t nks = (K + c.step - 1) / c.step;
     for (int64_t sp = 1; sp <= (allow_split ? c.max_splits : 1); sp *= 2) {
@@ -2395,7 +2399,9 @@ hipError_t contraction(const uint16_t *A, int64_t T, int64_t K, const uint32_t *
                        const float *tinfo_in = nullptr, float *RS = nullptr, int rs_w = 0) {
   float *tinfo = const_cast<float *>(tinfo_in);
   constexpr bool kFwd = kMode == kMid || kMode == kMidSave || kMode == kOut || kMode == kOutSave;
-  const ContractionPlan p = plan_contraction(T, K, N, P != nullptr, device_cus(), kFwd && P);
+  constexpr bool kFirst = kMode == kMid || kMode == kMidSave;
+  const ContractionPlan p =
+      plan_contraction(T, K, N, P != nullptr, device_cus(), kFwd && P, kFirst);
   if (p.splits > 1 && p.bn == BN && p.bm != 64) return hipErrorInvalidValue;  // see bingemm_kernel
   const int64_t tiles = (int64_t)p.gx * p.gy;
   const dim3 g = p.mix_full > 0
@@ -2403,7 +2409,6 @@ hipError_t contraction(const uint16_t *A, int64_t T, int64_t K, const uint32_t *
                      : dim3(p.gx, p.gy, (unsigned)p.splits);
   // RS entries a token (the second product's; the first writes its own) and
   // their row length
-  constexpr bool kFirst = kMode == kMid || kMode == kMidSave;
   const int w = kFirst ? rs_width(p) : rs_w;
   const int64_t rw = kFirst ? N : K;  // the intermediate's width
   const int nb = w > 0 ? (int)((rw + w - 1) / w) : 0, ld = w > 0 ? rs_ld(rw, w) : 0;
@@ -2523,7 +2528,7 @@ struct FwdPlans {
   ContractionPlan g1, g2;
 };
 FwdPlans forward_plans(int64_t m, int64_t n, int64_t r, int64_t T, int cus) {
-  return FwdPlans{plan_contraction(T, n, r, true, cus, true),
+  return FwdPlans{plan_contraction(T, n, r, true, cus, true, true),
                   plan_contraction(T, r, m, true, cus, true)};
 }
 
@@ -2625,7 +2630,7 @@ hipError_t launch_gemm(int64_t m, int64_t n, int64_t r, const uint32_t *Bu,
   if (T * n * 2 > 0x7fffffff || T * r * 2 > 0x7fffffff || m * (r / 32) * 4 > 0x7fffffff ||
       r * (n / 32) * 4 > 0x7fffffff)
     return hipErrorInvalidValue;
-  const int rs_w = rs_width(plan_contraction(T, n, r, true, device_cus(), true));
+  const int rs_w = rs_width(plan_contraction(T, n, r, true, device_cus(), true, true));
   const FwdWs w = forward_ws(ws, n, r, T, rs_w);
   hipError_t e = prepare_forward(n, s_in, x, T, w.xp, w.tinfo, s_mid, r, s);
   if (e != hipSuccess) return e;
@@ -2657,7 +2662,7 @@ hipError_t launch_forward_train(int64_t m, int64_t n, int64_t r, const uint32_t 
   if (T * n * 2 > 0x7fffffff || T * r * 2 > 0x7fffffff || m * (r / 32) * 4 > 0x7fffffff ||
       r * (n / 32) * 4 > 0x7fffffff)
     return hipErrorInvalidValue;
-  const int rs_w = rs_width(plan_contraction(T, n, r, true, device_cus(), true));
+  const int rs_w = rs_width(plan_contraction(T, n, r, true, device_cus(), true, true));
   const FwdWs w = forward_ws(ws, n, r, T, rs_w);
   uint16_t *v = static_cast<uint16_t *>(saved);
   float *z = reinterpret_cast<float *>(static_cast<uint8_t *>(saved) + align256((size_t)T * r * 2));
