@@ -228,10 +228,13 @@ AF1_API af1_status af1_linear_gemv_multi(const af1_factorized_linear *Ls, int32_
  * its bytes (16-byte aligned).  AF1_ERR_PLAN when the host plan is not a
  * plan of this library, AF1_ERR_HIP when the launch fails or the device
  * cannot hold every workgroup at once.  If a barrier ever timed out (a
- * workgroup that never arrived; only a device fault causes it) the kernel
- * ends early and leaves word 1 of the workspace non-zero; outputs are then
- * invalid and the workspace header must be zero-filled again.  Calls on
- * one workspace must not overlap in time.
+ * workgroup that never arrived) the kernel ends early and leaves word 1 of
+ * the workspace non-zero; outputs are then invalid and the workspace header
+ * must be zero-filled again.  A device fault causes it, and so can two layer
+ * streams in flight at once on one GPU, on whatever workspaces: each waits
+ * for all of its workgroups to be resident, so layer streams of one GPU must
+ * not overlap in time.  Every other call of this library ends by itself and
+ * may overlap with one.
  */
 #define AF1_STREAM_MAX_ITEMS 4096
 typedef struct af1_stream_item {

@@ -15,6 +15,9 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libaf1.so")
 NABF_LIB = os.path.join(HERE, "libaf1_nabf.so")
+# libaf1.so with -DAF1_TEST_BUILD: tests only, nothing else loads it
+TEST_LIB = os.path.join(HERE, "libaf1_test.so")
+TEST_SRCS = ("af1_gemv.hip",)  # the sources that it compiles differently
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
@@ -27,9 +30,9 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
          "-Wall", "-fvisibility=hidden", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 
-def _compile(src: str, verbose: bool) -> str:
-    obj = os.path.join(BUILD, os.path.basename(src) + ".o")
-    cmd = [HIPCC, *FLAGS, "-c", src, "-o", obj]
+def _compile(src: str, verbose: bool, test: bool = False) -> str:
+    obj = os.path.join(BUILD, os.path.basename(src) + (".test.o" if test else ".o"))
+    cmd = [HIPCC, *FLAGS, *(["-DAF1_TEST_BUILD"] if test else []), "-c", src, "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
     p = subprocess.run(cmd, capture_output=True, text=True)
@@ -51,16 +54,21 @@ def _link(out: str, objs, libs, verbose: bool) -> None:
 
 
 def build(verbose: bool = False) -> str:
-    """Compile every source; link libaf1.so (the layer) and libaf1_nabf.so
-    (the offline NABF building blocks, which also need rocBLAS and rocSOLVER
-    and reuse the sign-packing kernel).  Returns the path of libaf1.so."""
+    """Compile every source; link libaf1.so (the layer), its test build
+    libaf1_test.so, and libaf1_nabf.so (the offline NABF building blocks, which
+    also need rocBLAS and rocSOLVER and reuse the sign-packing kernel).  Returns
+    the path of libaf1.so."""
     os.makedirs(BUILD, exist_ok=True)
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
-    with cf.ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
+    with cf.ThreadPoolExecutor(max_workers=8) as ex:
+        tests = {s: ex.submit(_compile, s, verbose, True)
+                 for s in srcs if os.path.basename(s) in TEST_SRCS}
         objs = dict(zip(srcs, ex.map(lambda s: _compile(s, verbose), srcs)))
     nabf_src = os.path.join(CSRC, "af1_nabf.hip")
     pack_src = os.path.join(CSRC, "af1_pack.hip")
     _link(LIB, [o for s, o in objs.items() if s != nabf_src], [], verbose)
+    _link(TEST_LIB, [tests[s].result() if s in tests else o for s, o in objs.items()
+                     if s != nabf_src], [], verbose)
     _link(NABF_LIB, [objs[nabf_src], objs[pack_src]],
           ["-L/opt/rocm/lib", "-lrocsolver", "-lrocblas"], verbose)
     return LIB

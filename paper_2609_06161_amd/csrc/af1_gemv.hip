@@ -248,6 +248,14 @@ __device__ __forceinline__ void store_unit(uint8_t *slot_base, int h, const floa
 // store and one load, where a kernel boundary costs the first kernel's last
 // store, about 1.1 us, and the second's cold start.
 //
+// Nothing orders the start of one launch's workgroups against another
+// stream's, XCD by XCD: the first product's workgroups may be kept out by work
+// that itself waits for the units on which this launch waits (a layer stream,
+// other calls like this one).  So the wait is bounded: after kLinkPolls polls a
+// workgroup of the second product computes what it lacks of the first, the
+// same values by the same code, stored to the same words.  Every workgroup so
+// ends by itself, whatever else is or is not resident.
+//
 // There are two buffers.  A call uses the one of its number's parity and
 // clears the other (whose readers ended with the call before).  The number is
 // drawn by an atomic add a workgroup on one of 16 words (64 bits, their own
@@ -265,12 +273,21 @@ constexpr int kLinkSlots = 16, kLinkSlotWords = 32;
 constexpr int kLinkTickets = kMaxCounters;  // word offset in the first half
 constexpr int kLinkData = kLinkTickets + kLinkSlots * kLinkSlotWords;  // in each half
 constexpr int kLinkWords = kHeaderHalf - kLinkData;
-// Polls (about a microsecond each) before giving up with NaN.  A first-stage
-// workgroup may have to wait for another stream's kernel to leave its units
-// while second-stage ones already poll elsewhere, so the limit is far above
-// any kernel's time.
-constexpr int kLinkSpins = 1 << 24;
-constexpr uint32_t kLinkNan = 0x7fc00000u;
+// Polls of a wait (about a microsecond each) before the values are computed
+// instead: far above a first product's time (2 to 3 us), far below a stream
+// barrier's limit.  The test build does not wait, and starts the first product
+// late (by kLinkLate sleeps of about 4 us).
+#ifdef AF1_TEST_BUILD
+constexpr int kLinkPolls = 0, kLinkLate = 16;
+#else
+constexpr int kLinkPolls = 64, kLinkLate = 0;
+#endif
+
+// What a workgroup of a linked launch shares in LDS: this call's buffer, and
+// whether values are missing: in a wave's wait, or of a task.
+struct LinkState {
+  int buf, missing;
+};
 
 __device__ __forceinline__ void store_device_word(uint32_t *p, uint32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -301,16 +318,24 @@ __device__ __forceinline__ int fresh_zero() {
   return z;
 }
 
+// The same value, uniform, that the compiler takes for another one: code that a
+// launch hardly ever reaches then shares no register with the code before it.
+template <typename T>
+__device__ __forceinline__ T fresh(T v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
+
 // Waits until any of the wave's words (a lane's byte offset off, kOob for none)
 // is set: a light poll in front of the real loads, so that waiting waves leave
-// the memory path to the first stage, until its first values arrive.  False after kLinkSpins polls.
-__device__ __forceinline__ bool link_probe(__amdgpu_buffer_rsrc_t res, int off) {
-  for (int it = 0; it < kLinkSpins; ++it) {
+// the memory path to the first stage, until its first values arrive.  At most
+// kLinkPolls waits.
+__device__ __forceinline__ void link_probe(__amdgpu_buffer_rsrc_t res, int off) {
+  for (int it = 0; it < kLinkPolls; ++it) {
     const uint32_t v = __builtin_amdgcn_raw_buffer_load_b32(res, off, fresh_zero(), kDeviceScope);
-    if (__any(v != 0u) || __all(off == kOob)) return true;
+    if (__any(v != 0u) || __all(off == kOob)) return;
     __builtin_amdgcn_s_sleep(1);
   }
-  return false;
 }
 
 // Workgroup blk of blks clears its share of a link buffer.
@@ -319,6 +344,21 @@ __device__ __forceinline__ void link_clear(uint32_t *buf, int blk, int blks) {
   for (int i = blk * (int)blockDim.x + (int)threadIdx.x; i < kLinkWords / 4;
        i += blks * (int)blockDim.x)
     p[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// Whether the words of 16 rows (p: the first, left: rows from there on) are all
+// set; the whole workgroup asks and gets one answer.
+__device__ __forceinline__ bool link_set(LinkState *ls, const uint32_t *p, int left) {
+  const int t = (int)threadIdx.x;
+  if (t == 0) ls->missing = 0;
+  __syncthreads();
+  if (t < kTileRows && t < left &&
+      __hip_atomic_load(p + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u)
+    ls->missing = 1;
+  __syncthreads();
+  const bool set = ls->missing == 0;
+  __syncthreads();
+  return set;
 }
 
 // Output modes of a stage launch.
@@ -427,25 +467,28 @@ __device__ __forceinline__ void stage_signs(SignRegs &sg, const uint32_t *__rest
 
 // kLink: the two stages of a layer in one launch (gemv_fused_kernel), the
 // intermediate passed through the link (see kLinkNone above): kLinkOut stores it
-// there, kLinkIn waits for it there.
+// there (link_draw: in the buffer of the ticket it draws, else of ls->buf),
+// kLinkIn waits for it in ls->buf's; false is returned when the wait ended
+// without all of it, before anything was written.
+// kRare: code that a launch hardly ever reaches.
 // kLoop: a wave may own more than kMaxGroups groups; they are taken in
 // chunks of kMaxGroups, the next chunk's sign words loading while the
 // current chunk's products run (the stream kernel, whose persistent
 // workgroups cover long rows without splitting them into slabs).
 template <bool kInX, bool kOutY, bool kHiLoCols, bool kMulti, bool kCoherent = false,
-          bool kLoop = false, int kLink = kLinkNone>
-__device__ __forceinline__ void stage_body(
+          bool kLoop = false, int kLink = kLinkNone, bool kRare = false>
+__device__ __forceinline__ bool stage_body(
     const uint32_t *__restrict__ M, const void *__restrict__ in,
     const uint16_t *__restrict__ s_in, const uint16_t *__restrict__ row_scale, int rows,
     int wpr, int slab_words, int b, int rt_log2_arg, int nslabs, int mode, int in_parts,
     void *__restrict__ out, float *__restrict__ part, uint32_t *__restrict__ cnt, int group,
     int slab, int red_off = 0, const SignRegs *pre = nullptr, uint32_t *link = nullptr,
-    int link_grid = 0, int link_blk = 0, int link_blks = 0) {
+    LinkState *ls = nullptr, bool link_draw = false, int link_blk = 0, int link_blks = 0) {
   constexpr int kInAux = kCoherent || kLink == kLinkIn ? kDeviceScope : 0;
-  __shared__ int s_link;  // this call's link buffer
   const int rt_log2 = kMulti ? rt_log2_arg : 0;
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-  const int tid = threadIdx.x;
+  int tid = threadIdx.x;
+  if (kRare) asm volatile("" : "+v"(tid));  // see fresh()
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: wave-uniform
   const Role R = make_role(wave, group, slab, rt_log2, wpr, slab_words);
@@ -495,14 +538,16 @@ __device__ __forceinline__ void stage_body(
     // The weights do not depend on the first product: they travel while it
     // runs, but behind the ticket, so that the first product's own loads go
     // first.  The buffer that the call before used is cleared for the next.
-    if (tid == 0) s_link = link_ticket(link, link_grid);
-    __syncthreads();
-    load_signs();
+    if (link_draw) {
+      if (tid == 0) *ls = LinkState{link_ticket(link, (int)gridDim.x), 0};
+      __syncthreads();
+    }
+    if (!kRare) load_signs();
     load_row_scales(rscale_bits, row_scale, rows, group, rt_log2, b,
                     kMulti ? (((16 << rt_log2) * b + kThreads - 1) / kThreads) : 1);
-    uint32_t *mine = link_buffer(link, s_link);
-    link_clear(link_buffer(link, s_link ^ 1), link_blk, link_blks);
-    in = mine;
+    const int buf = ls->buf;
+    if (link_draw) link_clear(link_buffer(link, buf ^ 1), link_blk, link_blks);
+    in = link_buffer(link, buf);
   }
 
   // 2. Stage the input columns as bf16 hi/lo (p, p+16) pairs, one 144-byte
@@ -547,8 +592,8 @@ __device__ __forceinline__ void stage_body(
         const int wl = (R.cw + R.wpt * i) * kGroupWords + (rem >> 1);
         return wl < w_count ? (w_begin + wl) * 32 + 8 * (rem & 1) + 2 * qq : -1;
       };
-      int spins = link_probe(xres, column(0) >= 0 ? column(0) * 4 : kOob) ? 0 : kLinkSpins;
-      for (;; ++spins) {
+      link_probe(xres, column(0) >= 0 ? column(0) * 4 : kOob);
+      for (int polls = 0;; ++polls) {
         const int z = fresh_zero();
         u32x2 ra[kMaxGroups], rb[kMaxGroups], rc[kMaxGroups], rd[kMaxGroups];
 #pragma unroll
@@ -580,7 +625,6 @@ __device__ __forceinline__ void stage_body(
             v[3] += __uint_as_float(rd[i][1]);
           }
           there = there && (set || col < 0);
-          if (spins >= kLinkSpins) v[0] = __uint_as_float(kLinkNan);
           const uint32_t h0 = pack_bf16x2(v[0], v[2]), h1 = pack_bf16x2(v[1], v[3]);
           const uint32_t l0 =
               pack_bf16x2(v[0] - bf16_to_f32(h0 & 0xffffu), v[2] - bf16_to_f32(h0 >> 16));
@@ -591,8 +635,13 @@ __device__ __forceinline__ void stage_body(
           *reinterpret_cast<uint2 *>(dst) = make_uint2(h0, h1);
           *reinterpret_cast<uint2 *>(dst + 32) = make_uint2(l0, l1);
         }
-        if (__all(there) || spins >= kLinkSpins) break;
+        if (__all(there)) break;
+        if (polls >= kLinkPolls) {
+          if (lane == 0) ls->missing = 1;
+          break;
+        }
       }
+      if (kRare) load_signs();
     } else if (kHiLoCols && !shared && b == 1) {
       // One batch row: the 64 lanes share a group's 16 units, a quarter
       // unit each (columns c, c+1 and their partners c+16, c+17), so the
@@ -628,7 +677,7 @@ __device__ __forceinline__ void stage_body(
         }
       }
       if (c0 == 0) load_signs();
-      if (kLink == kLinkOut && tid == 0) ticket = link_ticket(link, link_grid);
+      if (kLink == kLinkOut && link_draw && tid == 0) ticket = link_ticket(link, (int)gridDim.x);
 #pragma unroll
       for (int i = 0; i < kMaxGroups; ++i) {
         if (c0 + i >= R.my_groups) break;  // uniform
@@ -662,7 +711,7 @@ __device__ __forceinline__ void stage_body(
       }
     } else {
       load_signs();
-      if (kLink == kLinkOut && tid == 0) ticket = link_ticket(link, link_grid);
+      if (kLink == kLinkOut && link_draw && tid == 0) ticket = link_ticket(link, (int)gridDim.x);
       // pass stride and this thread's first unit
       const int stride = shared ? 2 * kThreads : 128;
       const int first = shared ? tid : lane;
@@ -846,10 +895,12 @@ __device__ __forceinline__ void stage_body(
   if (red_off == 0) __syncthreads();  // uniform
   reinterpret_cast<float4 *>(lds + red_off)[wave * kRedLanes + lane + (lane >> 4)] =
       make_float4(tot[0], tot[1], tot[2], tot[3]);
-  if (kLink == kLinkOut && tid == 0) s_link = ticket;
+  if (kLink == kLinkOut && link_draw && tid == 0) ls->buf = ticket;
   __syncthreads();
+  int missing = 0;
+  if (kLink == kLinkIn) missing = ls->missing;  // uniform
   uint32_t *link_out = nullptr;
-  if constexpr (kLink == kLinkOut) link_out = link_buffer(link, s_link);
+  if constexpr (kLink == kLinkOut) link_out = link_buffer(link, ls->buf);
   const float *redf = reinterpret_cast<const float *>(lds + red_off);
   float sum[kMaxOutPerThread];
 #pragma unroll
@@ -874,6 +925,7 @@ __device__ __forceinline__ void stage_body(
     }
   }
 
+  if (kLink == kLinkIn && missing != 0) return false;  // (read beside the sums)
   if (mode == kModeLastSlab) {
     // Publish this slab's partial sums; the last slab of the workgroup's
     // rows to arrive adds all partials in slab order and resets the counter.
@@ -892,7 +944,7 @@ __device__ __forceinline__ void stage_body(
       s_last = __hip_atomic_fetch_add(&cnt[group], 1u, __ATOMIC_RELAXED,
                                       __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(nslabs - 1);
     __syncthreads();
-    if (!s_last) return;
+    if (!s_last) return true;
     // Device-scope loads of every slab's partial, issued before any is
     // added (the slab count is small: at most kMaxSlabsLoaded per pass).
     const __amdgpu_buffer_rsrc_t pres = buffer_rsrc(part, (int)min((int64_t)nslabs * b * rows * 4, (int64_t)0x7fffffff));
@@ -946,6 +998,7 @@ __device__ __forceinline__ void stage_body(
       }
     }
   }
+  return true;
 }
 
 // What a stage launch needs before its first loads, in one word: the batch (5
@@ -991,17 +1044,43 @@ __global__ __launch_bounds__(kThreads, 4) void gemv_fused_kernel(
     const uint32_t *__restrict__ Bu, const uint16_t *__restrict__ s_out, int m, int wpr2,
     int slab2, int red2, uint16_t *__restrict__ y) {
   // (the batch is 1; the first product's arguments first, see gemv_stage_kernel)
+  __shared__ LinkState ls;
   const int id = (int)blockIdx.x;
   if (id < G1) {
+    for (int i = 0; i < kLinkLate; ++i) __builtin_amdgcn_s_sleep(127);
     const int slab = id >= groups1 ? 1 : 0;
     stage_body<true, false, true, false, false, false, kLinkOut>(
         Bv, x, s_in, s_mid, r, wpr1, slab1, 1, 0, nslabs1, nslabs1 > 1 ? kModePartial : kModeFinal,
-        1, nullptr, nullptr, nullptr, id - slab * groups1, slab, red1, nullptr, hdr, G);
-  } else {
-    stage_body<false, true, true, false, false, false, kLinkIn>(
-        Bu, nullptr, nullptr, s_out, m, wpr2, slab2, 1, 0, 1, kModeFinal, nslabs1, y, nullptr,
-        nullptr, id - G1, 0, red2, nullptr, hdr, G, id - G1, G - G1);
+        1, nullptr, nullptr, nullptr, id - slab * groups1, slab, red1, nullptr, hdr, &ls, true);
+    return;
   }
+  const int blk = id - G1, blks = G - G1;
+  if (stage_body<false, true, true, false, false, false, kLinkIn>(
+          Bu, nullptr, nullptr, s_out, m, wpr2, slab2, 1, 0, 1, kModeFinal, nslabs1, y, nullptr,
+          nullptr, blk, 0, red2, nullptr, hdr, &ls, true, blk, blks))
+    return;
+  // The tasks whose values are not there yet, from a start of this workgroup's
+  // own, so that several workgroups share them.  After that every value has
+  // been seen or stored here, so the next wait ends.
+  do {
+    __syncthreads();  // ls.missing has been read, and the LDS is free
+    int t = (int)((int64_t)blk * G1 / blks);
+    for (int k = 0; k < G1; ++k, t = t + 1 == G1 ? 0 : t + 1) {
+      const int slab = t >= groups1 ? 1 : 0, row0 = (t - slab * groups1) * kTileRows;
+      if (link_set(&ls, link_buffer(hdr, ls.buf) + (size_t)slab * r + row0, r - row0)) continue;
+      stage_body<true, false, true, false, false, false, kLinkOut, true>(
+          fresh(Bv), fresh(x), fresh(s_in), fresh(s_mid), fresh(r), fresh(wpr1), fresh(slab1), 1, 0,
+          nslabs1, nslabs1 > 1 ? kModePartial : kModeFinal, 1, nullptr, nullptr, nullptr,
+          t - slab * groups1, slab, fresh(red1), nullptr, hdr, &ls, false);
+      __syncthreads();  // LDS is reused by the next task
+    }
+    wait_memory();
+    if (threadIdx.x == 0) ls.missing = 0;
+    __syncthreads();
+  } while (!stage_body<false, true, true, false, false, false, kLinkIn, true>(
+      fresh(Bu), nullptr, nullptr, fresh(s_out), fresh(m), fresh(wpr2), fresh(slab2), 1, 0, 1,
+      kModeFinal, nslabs1, y, nullptr, nullptr, fresh(blk), 0, fresh(red2), nullptr, hdr, &ls,
+      false));
 }
 
 // One stage of several layers that share the input width (the segments):
@@ -1224,9 +1303,8 @@ hipError_t launch_stage(const StageArgs &a, const StagePlan &p, hipStream_t s) {
 
 // Whether a layer's two stages run as one launch: one row tile per workgroup in
 // both, no last-slab reduction, the intermediate fits a link buffer, every
-// ticket word gets a workgroup, and at most two workgroups a unit, so that all
-// of them are resident at once (where their LDS allows two a unit).  Measured at b = 1 in a graph, one launch
-// against two: 1024^2 4.9 / 5.2 us, 1024x4096 5.05 / 5.6, 2048^2 5.1 / 5.4,
+// ticket word gets a workgroup, and at most two workgroups a unit.  Measured at
+// b = 1 in a graph, one launch against two: 1024^2 4.9 / 5.2 us, 1024x4096 5.05 / 5.6, 2048^2 5.1 / 5.4,
 // 2048x4096 5.4 / 5.9, 3072^2 5.6 / 5.9, 4096^2 (508 workgroups) 5.8 / 6.2; past
 // the line it turns (4096x5120 7.3 / 7.2, 6144x4096 7.7 / 7.6, 8192^2 10.4 /
 // 9.7).  A call from the host is 2.6 us shorter in one launch (4096^2 11.5 ->
