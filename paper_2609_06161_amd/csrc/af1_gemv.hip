@@ -1303,15 +1303,21 @@ hipError_t launch_stage(const StageArgs &a, const StagePlan &p, hipStream_t s) {
 
 // Whether a layer's two stages run as one launch: one row tile per workgroup in
 // both, no last-slab reduction, the intermediate fits a link buffer, every
-// ticket word gets a workgroup, and at most two workgroups a unit.  Measured at
-// b = 1 in a graph, one launch against two: 1024^2 4.9 / 5.2 us, 1024x4096 5.05 / 5.6, 2048^2 5.1 / 5.4,
+// ticket word gets a workgroup, and at most two workgroups a unit, whose LDS
+// lets two share one (only staged rows of more than 15648 columns take too much;
+// then half the grid waits for a unit: 4096x16384 r=4096 11.7 us against 10.7
+// in two launches, 2048x16000 11.0 against 10.6).  Measured at b = 1 in a graph, one launch against two: 1024^2 4.9 / 5.2 us, 1024x4096 5.05 / 5.6, 2048^2 5.1 / 5.4,
 // 2048x4096 5.4 / 5.9, 3072^2 5.6 / 5.9, 4096^2 (508 workgroups) 5.8 / 6.2; past
 // the line it turns (4096x5120 7.3 / 7.2, 6144x4096 7.7 / 7.6, 8192^2 10.4 /
 // 9.7).  A call from the host is 2.6 us shorter in one launch (4096^2 11.5 ->
 // 8.9).  Batches above 1 gain nothing (3584^2 at b = 2: 8.6 / 8.3 before both
 // forms got shorter): the waiting workgroups poll and convert b times as many
 // words.
-bool fused_ok(const StagePlan &p1, const StagePlan &p2, int64_t m, int64_t r, int64_t b, int cus) {
+bool fused_ok(const StagePlan &p1, const StagePlan &p2, int64_t m, int64_t n, int64_t r, int64_t b,
+              int cus) {
+  int red = 0;
+  const size_t l1 = stage_lds(p1, b, (int)(n / 32), &red), l2 = stage_lds(p2, b, (int)(r / 32), &red);
+  if (2 * ((l1 > l2 ? l1 : l2) + kStaticLdsReserve) > (size_t)kLdsPerCu) return false;
   const int64_t parts = p1.mode == kModePartial ? p1.nslabs : 1;
   const int64_t g = (r + kTileRows - 1) / kTileRows * parts + (m + kTileRows - 1) / kTileRows;
   return b == 1 && p1.rt_log2 == 0 && p2.rt_log2 == 0 && p1.mode != kModeLastSlab &&
@@ -1515,7 +1521,7 @@ hipError_t launch_gemv(int64_t m, int64_t n, int64_t r, const uint32_t *Bu,
   const StageArgs s2{Bu, t, nullptr, s_out, (int)m, (int)(r / 32), (int)b, tparts, y,
                      reinterpret_cast<float *>(base + L.part2),
                      reinterpret_cast<uint32_t *>(base + L.cnt2)};
-  if (link && fused_ok(L.p1, L.p2, m, r, b, cus))
+  if (link && fused_ok(L.p1, L.p2, m, n, r, b, cus))
     return launch_fused(s1, s2, L.p1, L.p2, reinterpret_cast<uint32_t *>(base), s);
   const hipError_t e = launch_stage<true, false>(s1, L.p1, s);
   if (e != hipSuccess) return e;
@@ -2012,3 +2018,12 @@ hipError_t launch_stream(const void *plan_dev, const void *plan_host, hipStream_
 }
 
 }  // namespace af1
+
+#ifdef AF1_TEST_BUILD
+// Launches of af1_linear_gemv for this shape and batch.
+extern "C" AF1_API int32_t af1_test_gemv_launches(int64_t m, int64_t n, int64_t r, int64_t b) {
+  const int cus = af1::device_cus();
+  const af1::WsLayout L = af1::ws_layout(m, n, r, b, cus);
+  return af1::fused_ok(L.p1, L.p2, m, n, r, b, cus) ? 1 : 2;
+}
+#endif

@@ -17,3 +17,16 @@ def oracle():
     import oracle as _oracle
     _oracle._load()
     return _oracle
+
+
+@pytest.fixture(scope="session")
+def test_lib():
+    """The library's test build, whose af1_test_* queries tell what its plans
+    choose (plans are the same in both builds)."""
+    import ctypes
+
+    from paper_2609_06161_amd import build_lib
+    L = ctypes.CDLL(build_lib.TEST_LIB)
+    I = ctypes.c_int64
+    L.af1_test_gemv_launches.argtypes = [I] * 4
+    return L
