@@ -1265,13 +1265,16 @@ struct StageArgs {
 // The LDS of a stage launch: the staged input and the cross-wave sums.  With
 // one row tile per workgroup the sums get their own region past the staged
 // input when it fits (one barrier instead of two): *red_off > 0.
-size_t stage_lds(const StagePlan &p, int64_t b, int wpr, int *red_off) {
+// keep_two: not where that takes the second workgroup from a compute unit.
+size_t stage_lds(const StagePlan &p, int64_t b, int wpr, int *red_off, bool keep_two = false) {
   const int sw = p.slab_words < wpr ? p.slab_words : wpr;
   size_t lds = lds_bytes_for(b, sw);
   *red_off = 0;
   if (p.rt_log2 == 0) {
     const size_t stage = (lds_stage_bytes(b, sw) + 15) & ~(size_t)15;
-    if (stage + kRedBytes <= (size_t)kLdsBudget) {
+    const bool two = 2 * (lds + kStaticLdsReserve) <= (size_t)kLdsPerCu;
+    const bool still = 2 * (stage + kRedBytes + kStaticLdsReserve) <= (size_t)kLdsPerCu;
+    if (stage + kRedBytes <= (size_t)kLdsBudget && !(keep_two && two && !still)) {
       *red_off = (int)stage;
       lds = stage + kRedBytes;
     }
@@ -1306,8 +1309,9 @@ hipError_t launch_stage(const StageArgs &a, const StagePlan &p, hipStream_t s) {
 // ticket word gets a workgroup, and at most two workgroups a unit, whose LDS
 // lets two share one (only staged rows of more than 15648 columns take too much;
 // then half the grid waits for a unit: 4096x16384 r=4096 11.7 us against 10.7
-// in two launches, 2048x16000 11.0 against 10.6).  Measured at b = 1 in a graph, one launch against two: 1024^2 4.9 / 5.2 us, 1024x4096 5.05 / 5.6, 2048^2 5.1 / 5.4,
-// 2048x4096 5.4 / 5.9, 3072^2 5.6 / 5.9, 4096^2 (508 workgroups) 5.8 / 6.2; past
+// in two launches, 2048x16000 11.0 against 10.6).  Measured at b = 1 in a
+// graph, one launch against two: 1024^2 4.9 / 5.2 us, 1024x4096 5.05 / 5.6,
+// 2048^2 5.1 / 5.4, 2048x4096 5.4 / 5.9, 3072^2 5.6 / 5.9, 4096^2 (508 workgroups) 5.8 / 6.2; past
 // the line it turns (4096x5120 7.3 / 7.2, 6144x4096 7.7 / 7.6, 8192^2 10.4 /
 // 9.7).  A call from the host is 2.6 us shorter in one launch (4096^2 11.5 ->
 // 8.9).  Batches above 1 gain nothing (3584^2 at b = 2: 8.6 / 8.3 before both
@@ -1342,11 +1346,23 @@ hipError_t launch_fused(const StageArgs &a1, const StageArgs &a2, const StagePla
   return hipGetLastError();
 }
 
+int row_groups(int64_t rows, const StagePlan &p) {
+  const int rows_wg = kTileRows << p.rt_log2;
+  return (int)((rows + rows_wg - 1) / rows_wg);
+}
+
+// The LDS of a launch of several layers with `groups` row groups.  (Layers of
+// 15700 to 16384 columns at b=1: two of 16384 -> 4096, 17.1 us a call with the
+// sums' region, 15.6 without.)
+size_t segs_lds(const StagePlan &p, int64_t b, int max_wpr, int64_t groups, int *red_off) {
+  return stage_lds(p, b, max_wpr, red_off, groups * p.nslabs > device_cus());
+}
+
 template <bool kInX, bool kOutY>
 hipError_t launch_segs(const Segs &sg, const StagePlan &p, int b, int max_wpr, int in_parts,
                        hipStream_t s) {
   int red_off = 0;
-  const size_t lds = stage_lds(p, b, max_wpr, &red_off);
+  const size_t lds = segs_lds(p, b, max_wpr, sg.groups, &red_off);
   dim3 grid((unsigned)sg.groups, (unsigned)p.nslabs);
   auto end = [&](int i) { return i + 1 < sg.count ? sg.s[i + 1].group_begin : INT_MAX; };
   auto go = [&](auto kernel) -> hipError_t {
@@ -1447,15 +1463,14 @@ hipError_t launch_gemv_multi(int count, const int64_t *m, const int64_t *r, int6
   const int tparts = L.p1.mode == kModePartial ? L.p1.nslabs : 1;
   Segs s1{}, s2{};
   s1.count = s2.count = count;
-  const int rw1 = kTileRows << L.p1.rt_log2, rw2 = kTileRows << L.p2.rt_log2;
   int g1 = 0, g2 = 0, wpr2 = 0;
   for (int i = 0; i < count; ++i) {
     float *t = reinterpret_cast<float *>(base + L.t[i]);
     Seg &a = s1.s[i], &c = s2.s[i];
     a.group_begin = g1;
     c.group_begin = g2;
-    g1 += (int)((r[i] + rw1 - 1) / rw1);
-    g2 += (int)((m[i] + rw2 - 1) / rw2);
+    g1 += row_groups(r[i], L.p1);
+    g2 += row_groups(m[i], L.p2);
     a.rows = (int)r[i];
     a.wpr = (int)(n / 32);
     a.M = Bv[i];
@@ -2025,5 +2040,17 @@ extern "C" AF1_API int32_t af1_test_gemv_launches(int64_t m, int64_t n, int64_t 
   const int cus = af1::device_cus();
   const af1::WsLayout L = af1::ws_layout(m, n, r, b, cus);
   return af1::fused_ok(L.p1, L.p2, m, n, r, b, cus) ? 1 : 2;
+}
+
+// LDS bytes a workgroup of af1_linear_gemv_multi's first launch requests for
+// `count` equal layers.
+extern "C" AF1_API int64_t af1_test_multi_lds(int64_t m, int64_t n, int64_t r, int32_t count,
+                                              int64_t b) {
+  if (count < 1 || count > af1::kMaxSegs) return -1;
+  int64_t ms[af1::kMaxSegs], rs[af1::kMaxSegs];
+  for (int i = 0; i < count; ++i) ms[i] = m, rs[i] = r;
+  const af1::MultiLayout L = af1::multi_layout(ms, rs, count, n, b, af1::device_cus());
+  int red_off = 0;
+  return (int64_t)af1::segs_lds(L.p1, b, (int)(n / 32), count * af1::row_groups(r, L.p1), &red_off);
 }
 #endif

@@ -29,4 +29,6 @@ def test_lib():
     L = ctypes.CDLL(build_lib.TEST_LIB)
     I = ctypes.c_int64
     L.af1_test_gemv_launches.argtypes = [I] * 4
+    L.af1_test_multi_lds.argtypes = [I, I, I, ctypes.c_int32, I]
+    L.af1_test_multi_lds.restype = I
     return L

@@ -16,3 +16,14 @@ import pytest
 ])
 def test_one_launch_decode(test_lib, m, n, r, b, launches):
     assert test_lib.af1_test_gemv_launches(m, n, r, b) == launches
+
+
+@pytest.mark.parametrize("m,n,r,count,two", [
+    (4096, 16384, 3264, 2, True), (2560, 16384, 2176, 3, True),
+    (4096, 15680, 3232, 2, True), (4096, 4096, 2016, 3, True),
+    (4096, 16384, 2048, 2, False),   # no more workgroups than units
+])
+def test_fused_projections_leave_room_for_two(test_lib, m, n, r, count, two):
+    """Where the launch has more workgroups than units, two fit a unit's LDS."""
+    lds = test_lib.af1_test_multi_lds(m, n, r, count, 1)
+    assert (2 * (lds + 256) <= 160 * 1024) == two
