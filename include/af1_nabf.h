@@ -89,6 +89,8 @@ AF1_API af1_status af1_nabf_surrogate(const float *W, int64_t m, int64_t n, cons
  * all-ones right vector: each pass forms u = |Z| v, w = |Z|^T u and
  * v = w / ||w|| (v is kept when w is zero); then left = |Z| v and right = v
  * (unit norm).  fp32 throughout.  iters in [0, AF1_NABF_MAX_POWER_ITERS].
+ * ws: what af1_nabf_workspace_bytes gives for a layer with such a factor is
+ * enough; the results do not depend on ws_bytes.
  *   Z : rows x cols fp32.  bits: rows * (cols/32) words.  left: rows.
  *   right: cols.
  */

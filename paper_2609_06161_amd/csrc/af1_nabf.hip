@@ -39,7 +39,8 @@ using af1::f32_to_f16;
 using af1::wave_sum;
 
 constexpr double kEps = 1e-12;   // residual-energy fraction and scale fits
-constexpr int kChunk = 64;       // rows per partial-sum tile
+constexpr int kChunkLog2 = 6;
+constexpr int kChunk = 1 << kChunkLog2;  // rows per partial-sum tile
 
 // ---------------------------------------------------------------------------
 // Device kernels
@@ -113,21 +114,61 @@ __global__ __launch_bounds__(256) void colsq_kernel(const uint16_t *__restrict__
   }
 }
 
+__device__ __forceinline__ float4 add4(const float4 &a, const float4 &b) {
+  return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+}
+__device__ __forceinline__ float add4(float a, float b) { return a + b; }
+
+// A sum of up to 16 terms, pushed in order, in pairs, pairs of pairs and so on;
+// terms that are not pushed count as zeros.  Whoever adds up aligned runs of
+// 1, 2, 4 or 8 of the terms first gets the same bits.
+template <typename V>
+struct TreeSum {
+  V level[4];
+  int count = 0;  // uniform
+  __device__ __forceinline__ void push(V v) {
+    bool held = false;
+#pragma unroll
+    for (int l = 0; l < 4; ++l) {
+      if (held) continue;
+      if (count >> l & 1) {
+        v = add4(level[l], v);
+      } else {
+        level[l] = v;
+        held = true;
+      }
+    }
+    if (!held) total = v;  // the sixteenth term
+    ++count;
+  }
+  __device__ __forceinline__ V sum(V zero) const {
+    V v = count >> 4 ? total : zero;
+#pragma unroll
+    for (int l = 0; l < 4; ++l)
+      if (count >> l & 1) v = add4(level[l], v);
+    return v;
+  }
+  V total;
+};
+
 // Column sums of partial rows: out[j] = sum over the chunks of
 // part[chunk][j], for up to two matrices in one launch (blocks below `split`
-// take the first).  A workgroup takes 64 columns: 16 float4 columns by 16
-// chunk groups (group g adds chunks g, g + 16, ..., eight loads in flight),
-// the groups added in order through LDS.  kRms: out = sqrt(sum / T), the
-// surrogate's column RMS.  One thread a column,
-// each chunk waited for in turn, took 16 us at 64 chunks x 2016 columns;
-// 512 chunks now take 4.3.
+// take the first).  A chunk is 1 << kSubLog2 (at most 16) consecutive rows of
+// part (the last one may have fewer of the `rows`), added up in pairs, pairs of
+// pairs and so on (TreeSum), so that the result does not depend on how finely
+// the chunks were split.  A workgroup takes
+// 64 columns: 16 float4 columns by 16 chunk groups (group g adds chunks g, g +
+// 16, ..., eight rows' loads or a chunk's in flight), the groups added in order through
+// LDS.  kRms: out = sqrt(sum / T), the surrogate's column RMS.  One thread a
+// column, each chunk waited for in turn, took 16 us at 64 rows x 2016 columns;
+// 512 rows now take 4.3.
 constexpr int kSumCols = 64;
 struct ColSum {
   const float *part;
   float *out;
-  int chunks, cols;
+  int rows, cols;
 };
-template <bool kRms>
+template <bool kRms, int kSubLog2>
 __global__ __launch_bounds__(256) void colsum_kernel(ColSum a, ColSum b, int split, int T) {
   __shared__ float4 red[16][17];
   const bool first = (int)blockIdx.x < split;  // uniform
@@ -136,20 +177,25 @@ __global__ __launch_bounds__(256) void colsum_kernel(ColSum a, ColSum b, int spl
   const int j = kSumCols * ((int)blockIdx.x - (first ? 0 : split)) + 4 * c4;
   const int jl = j < p.cols ? j : 0;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int k0 = g; k0 < p.chunks; k0 += 16 * 8) {
-    float4 v[8];
+  constexpr int kSub = 1 << kSubLog2, kLoads = kSub > 8 ? kSub : 8;
+  const int chunks = (p.rows + kSub - 1) / kSub;
+  for (int c0 = g; c0 < chunks; c0 += 16 * (kLoads / kSub)) {
+    float4 v[kLoads];
+    // load q: a row of chunk c0 + 16 (q / kSub)
+    auto row = [&](int q) { return (c0 + 16 * (q / kSub)) * kSub + q % kSub; };
 #pragma unroll
-    for (int q = 0; q < 8; ++q)
-      v[q] = *reinterpret_cast<const float4 *>(
-          p.part + (size_t)min(k0 + 16 * q, p.chunks - 1) * p.cols + jl);
+    for (int q = 0; q < kLoads; ++q)
+      v[q] = *reinterpret_cast<const float4 *>(p.part + (size_t)min(row(q), p.rows - 1) * p.cols +
+                                               jl);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const bool use = k0 + 16 * q < p.chunks;
-      s.x += use ? v[q].x : 0.f;
-      s.y += use ? v[q].y : 0.f;
-      s.z += use ? v[q].z : 0.f;
-      s.w += use ? v[q].w : 0.f;
-    }
+    for (int q = 0; q < kLoads; ++q)
+      if (row(q) >= p.rows) v[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int l = 1; l <= kSubLog2; ++l)
+#pragma unroll
+      for (int q = 0; q < kLoads >> l; ++q) v[q] = add4(v[2 * q], v[2 * q + 1]);
+#pragma unroll
+    for (int q = 0; q < kLoads / kSub; ++q) s = add4(s, v[q]);
   }
   red[g][c4] = s;
   __syncthreads();
@@ -211,8 +257,8 @@ __global__ __launch_bounds__(256) void abs_rowdot_kernel(const float *__restrict
   if (lane == 0) u[i] = s;
 }
 
-// One power-iteration pass of the SVID, Z read once.  A workgroup takes a
-// block of rows: for each row u = |Z_i| v (a reduction over the workgroup),
+// One power-iteration pass of the SVID, Z read once (kPass).  A workgroup takes
+// a block of rows: for each row u = |Z_i| v (a reduction over the workgroup),
 // then w += |Z_i| u from the same registers, and the block's w goes to
 // part[block].  colsum_kernel adds the blocks.  A thread holds kQ float4 of
 // every row (columns 4 (tid + threads q) ..), so kQ * threads * 4 >= cols;
@@ -225,17 +271,23 @@ __global__ __launch_bounds__(256) void abs_rowdot_kernel(const float *__restrict
 // Workgroup 0 stores v to `right`; where the others read `right` (w zero),
 // it stores the values that are there.
 //
-// kLast: the final left = |Z| v instead of w, and the signs of Z packed as
-// af1_pack does (eight lanes' sign nibbles make a word).
+// kRowDot: left = u = |Z| v instead of w.  kLast: that, the final left, and the
+// signs of Z packed as af1_pack does (eight lanes' sign nibbles make a word).
+// The sums are written as fmaf, so that every mode rounds them alike.
 //
 // Bound by the read of Z, which the last-level cache holds between passes at
 // calibration sizes.  Separate row and column passes with a finishing and a
 // normalising launch read Z twice: 43.7 us a pass at 4096 x 2016 (33 MB);
 // this pass takes 6.9 us there and the column sums 4.3 (kernel trace).
-template <int kQ, int kR, int kThreads, bool kLast>
+//
+// kPassTree: kPass whose workgroups take several runs of sub_rows rows, each
+// summed by itself and then as TreeSum does (the scratch has no row of part for
+// every run).
+constexpr int kPass = 0, kRowDot = 1, kLast = 2, kPassTree = 3;
+template <int kQ, int kR, int kThreads, int kMode>
 __global__ __launch_bounds__(kThreads) void svid_pass_kernel(
-    const float *__restrict__ Z, int rows, int cols, int rows_wg, const float *__restrict__ w,
-    float v0, float *right, float *__restrict__ part, float *__restrict__ left,
+    const float *__restrict__ Z, int rows, int cols, int rows_wg, int sub_rows,
+    const float *__restrict__ w, float v0, float *right, float *__restrict__ part, float *__restrict__ left,
     uint32_t *__restrict__ bits) {
   constexpr int kWaves = kThreads / 64;
   __shared__ float red[2][kR][kWaves];
@@ -267,7 +319,8 @@ __global__ __launch_bounds__(kThreads) void svid_pass_kernel(
 #pragma unroll
     for (int q = 0; q < kQ; ++q) {
       v[q] = *reinterpret_cast<const float4 *>(w + col[q]);
-      s += live[q] ? v[q].x * v[q].x + v[q].y * v[q].y + v[q].z * v[q].z + v[q].w * v[q].w : 0.f;
+      const float t = fmaf(v[q].w, v[q].w, fmaf(v[q].z, v[q].z, fmaf(v[q].y, v[q].y, v[q].x * v[q].x)));
+      s += live[q] ? t : 0.f;
     }
     s = wave_sum_dpp(s);
     if ((tid & 63) == 0) red[1][0][wave] = s;
@@ -296,6 +349,7 @@ __global__ __launch_bounds__(kThreads) void svid_pass_kernel(
   float4 acc[kQ];
 #pragma unroll
   for (int q = 0; q < kQ; ++q) acc[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+  TreeSum<float4> tree[kMode == kPassTree ? kQ : 1];
   // rows i .. i + kR - 1 (in z); the red buffers alternate, so one barrier a
   // batch is enough
   auto batch = [&](const float4 (&z)[kR][kQ], int i, int buf) {
@@ -304,10 +358,12 @@ __global__ __launch_bounds__(kThreads) void svid_pass_kernel(
     for (int r = 0; r < kR; ++r) {
       float s = 0.f;
 #pragma unroll
-      for (int q = 0; q < kQ; ++q)
-        s += live[q] ? fabsf(z[r][q].x) * v[q].x + fabsf(z[r][q].y) * v[q].y +
-                           fabsf(z[r][q].z) * v[q].z + fabsf(z[r][q].w) * v[q].w
-                     : 0.f;
+      for (int q = 0; q < kQ; ++q) {
+        const float4 f = z[r][q];
+        const float t = fmaf(fabsf(f.w), v[q].w, fmaf(fabsf(f.z), v[q].z,
+                             fmaf(fabsf(f.y), v[q].y, fabsf(f.x) * v[q].x)));
+        s += live[q] ? t : 0.f;
+      }
       u[r] = wave_sum_dpp(s);
     }
     if ((tid & 63) == 0) {
@@ -322,10 +378,10 @@ __global__ __launch_bounds__(kThreads) void svid_pass_kernel(
 #pragma unroll
       for (int k = 1; k < kWaves; ++k) t += red[buf][r][k];
       const bool use = i + r < i1;  // uniform
-      if constexpr (kLast) {
+      if constexpr (kMode == kRowDot || kMode == kLast) {
         if (use && tid == 0) left[i + r] = t;
 #pragma unroll
-        for (int q = 0; q < kQ; ++q) {
+        for (int q = 0; q < (kMode == kLast ? kQ : 0); ++q) {
           const float4 f = z[r][q];
           uint32_t n = (__float_as_uint(f.x) >> 31) | (__float_as_uint(f.y) >> 31) << 1 |
                        (__float_as_uint(f.z) >> 31) << 2 | (__float_as_uint(f.w) >> 31) << 3;
@@ -336,14 +392,22 @@ __global__ __launch_bounds__(kThreads) void svid_pass_kernel(
           if (use && live[q] && (tid & 7) == 0) bits[(size_t)(i + r) * (cols / 32) + col[q] / 32] = n;
         }
       } else {
-        const float uu = use ? t : 0.f;
 #pragma unroll
         for (int q = 0; q < kQ; ++q) {
           // a row past the block adds nothing (its data is another row's)
-          acc[q].x += use ? fabsf(z[r][q].x) * uu : 0.f;
-          acc[q].y += use ? fabsf(z[r][q].y) * uu : 0.f;
-          acc[q].z += use ? fabsf(z[r][q].z) * uu : 0.f;
-          acc[q].w += use ? fabsf(z[r][q].w) * uu : 0.f;
+          acc[q].x = use ? fmaf(fabsf(z[r][q].x), t, acc[q].x) : acc[q].x;
+          acc[q].y = use ? fmaf(fabsf(z[r][q].y), t, acc[q].y) : acc[q].y;
+          acc[q].z = use ? fmaf(fabsf(z[r][q].z), t, acc[q].z) : acc[q].z;
+          acc[q].w = use ? fmaf(fabsf(z[r][q].w), t, acc[q].w) : acc[q].w;
+        }
+      }
+    }
+    if constexpr (kMode == kPassTree) {
+      if ((i + kR - i0) % sub_rows == 0 || i + kR >= i1) {  // a run ends (sub_rows % kR == 0)
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) {
+          tree[q].push(acc[q]);
+          acc[q] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
       }
     }
@@ -355,25 +419,46 @@ __global__ __launch_bounds__(kThreads) void svid_pass_kernel(
     load(za, min(i + 2 * kR, i1 - 1));
     batch(zb, i + kR, 1);
   }
-  if constexpr (!kLast) {
+  if constexpr (kMode == kPass || kMode == kPassTree) {
 #pragma unroll
-    for (int q = 0; q < kQ; ++q)
+    for (int q = 0; q < kQ; ++q) {
+      if constexpr (kMode == kPassTree) acc[q] = tree[q].sum(make_float4(0.f, 0.f, 0.f, 0.f));
       if (live[q])
         *reinterpret_cast<float4 *>(part + (size_t)blockIdx.x * cols + col[q]) = acc[q];
+    }
   }
 }
 
-// part[chunk][j] = sum over the chunk's rows i of |Z[i][j]| u[i].
+// part[chunk][j] = sum over the chunk's rows i of |Z[i][j]| u[i]; every run of
+// sub_rows rows (4 to 64) is added up by itself first, the runs as TreeSum does.
+// Sixteen rows' loads in flight (rows % 32 == 0).
 __global__ __launch_bounds__(256) void abs_coldot_kernel(const float *__restrict__ Z, int64_t rows,
                                                          int cols, const float *__restrict__ u,
-                                                         float *__restrict__ part) {
+                                                         float *__restrict__ part, int sub_rows) {
   const int j = blockIdx.x * 256 + threadIdx.x;
   if (j >= cols) return;
   const int64_t i0 = (int64_t)blockIdx.y * kChunk;
   const int64_t i1 = min(rows, i0 + kChunk);
-  float s = 0.f;
-  for (int64_t i = i0; i < i1; ++i) s += fabsf(Z[i * cols + j]) * u[i];
-  part[(size_t)blockIdx.y * cols + j] = s;
+  TreeSum<float> s;
+  float t = 0.f;
+  for (int64_t k0 = i0; k0 < i1; k0 += 16) {
+    float z[16], uu[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      z[q] = Z[(k0 + q) * cols + j];
+      uu[q] = u[k0 + q];
+    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      t = fmaf(fabsf(z[q]), uu[q], t);
+      const int done = (int)(k0 - i0) + q + 1;  // uniform
+      if (q % 4 == 3 && (done % sub_rows == 0 || k0 + q + 1 == i1)) {
+        s.push(t);
+        t = 0.f;
+      }
+    }
+  }
+  part[(size_t)blockIdx.y * cols + j] = s.sum(0.f);
 }
 
 // w[j] = sum over chunks of part[chunk][j] (in order); sq[block] = the
@@ -751,45 +836,69 @@ size_t svid_layout(int64_t rows, int64_t cols, uint8_t *base, Ws *w) {
 
 // ---- building blocks (arguments already validated) ------------------------
 
-// Rows a workgroup of svid_pass_kernel takes: few enough for two workgroups
-// per compute unit, at least kSvidMinRows (below it the partial sums cost
-// more than the read of Z: every workgroup writes one row of them), and no
-// fewer than the scratch of part_floats holds (64 rows always fit).
-constexpr int kSvidMinRows = 4;
-int compute_units() {
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      cus <= 0)
-    return 256;
-  return cus;
-}
-int svid_rows_wg(int64_t rows, int64_t cols, size_t part_floats) {
-  int rw = kSvidMinRows;
-  while (rw < kChunk && ((rows + rw - 1) / rw > 2 * (int64_t)compute_units() ||
-                         (size_t)((rows + rw - 1) / rw) * cols > part_floats))
-    rw *= 2;
-  return rw;
+// log2 of the rows of a run, which svid_pass_kernel adds up row by row: one run
+// a workgroup gives two workgroups per compute unit of the device (512 in all);
+// at least 4 rows (below it the partial sums cost more than the read of Z:
+// every workgroup writes one row of them), at most a chunk.  From the shape
+// alone, so that the sums are grouped alike whatever the workspace.
+constexpr int kSvidWgs = 512;
+int svid_run_log2(int64_t rows) {
+  int l = 2;
+  while (l < kChunkLog2 && ((rows + (1 << l) - 1) >> l) > kSvidWgs) ++l;
+  return l;
 }
 
 template <int kQ, int kR, int kThreads>
 af1_status svid_fused(const float *Z, int64_t rows, int64_t cols, int iters, uint32_t *bits,
                       float *left, float *right, float *part, size_t part_floats, float *w,
                       hipStream_t s) {
-  const int rw = svid_rows_wg(rows, cols, part_floats);
-  const unsigned blocks = (unsigned)((rows + rw - 1) / rw);
+  // Rows a workgroup: a run, or as many as leave each workgroup a row of the
+  // scratch (a chunk always does).
+  const int run = svid_run_log2(rows);
+  int wl = run;
+  auto blocks_of = [&](int l) { return (unsigned)((rows + (1 << l) - 1) >> l); };
+  while (wl < kChunkLog2 && (size_t)blocks_of(wl) * cols > part_floats) ++wl;
+  // Too few workgroups that way (or 1024 threads, whose registers do not hold
+  // the tree): the pass ends at u, and a launch of its own, 256 columns a
+  // workgroup, adds up w; the same sums (10 passes on the least scratch, apart /
+  // in one: 192x4576, 3 workgroups, 122 / 368 us; 4096x2016, 64, 163 / 196;
+  // 8192x1024, 128, 176 / 151; 8192x4064, 128, 473 / 286).
+  const bool apart = wl > run && (blocks_of(wl) < 96 || kThreads == 1024);
   const unsigned cb = (unsigned)((cols + kSumCols - 1) / kSumCols);
   const float v0 = 1.0f / sqrtf((float)cols);
+  auto pass = [&](auto mode, int l, const float *wp) {
+    svid_pass_kernel<kQ, kR, kThreads, decltype(mode)::value><<<blocks_of(l), kThreads, 0, s>>>(
+        Z, (int)rows, (int)cols, 1 << l, 1 << run, wp, v0, right, part, left, bits);
+  };
+  using std::integral_constant;
   for (int it = 0; it < iters; ++it) {
-    svid_pass_kernel<kQ, kR, kThreads, false><<<blocks, kThreads, 0, s>>>(
-        Z, (int)rows, (int)cols, rw, it == 0 ? nullptr : w, v0, right, part, nullptr, nullptr);
+    const float *wp = it == 0 ? nullptr : w;
+    if (apart) {
+      pass(integral_constant<int, kRowDot>{}, run, wp);
+      CHECK_LAUNCH();
+      abs_coldot_kernel<<<dim3(blocks_for(cols), (unsigned)chunks_of(rows)), 256, 0, s>>>(
+          Z, rows, (int)cols, left, part, 1 << run);
+    } else if (wl > run) {
+      if constexpr (kThreads < 1024) pass(integral_constant<int, kPassTree>{}, wl, wp);
+    } else {
+      pass(integral_constant<int, kPass>{}, wl, wp);
+    }
     CHECK_LAUNCH();
-    const ColSum c{part, w, (int)blocks, (int)cols};
-    colsum_kernel<false><<<cb, 256, 0, s>>>(c, c, (int)cb, 1);
+    const int l = apart ? kChunkLog2 : wl;
+    const ColSum c{part, w, (int)blocks_of(l), (int)cols};
+    auto colsum = [&](auto sub) {
+      colsum_kernel<false, decltype(sub)::value><<<cb, 256, 0, s>>>(c, c, (int)cb, 1);
+    };
+    switch (kChunkLog2 - l) {
+      case 0: colsum(integral_constant<int, 0>{}); break;
+      case 1: colsum(integral_constant<int, 1>{}); break;
+      case 2: colsum(integral_constant<int, 2>{}); break;
+      case 3: colsum(integral_constant<int, 3>{}); break;
+      default: colsum(integral_constant<int, 4>{}); break;
+    }
     CHECK_LAUNCH();
   }
-  svid_pass_kernel<kQ, kR, kThreads, true><<<blocks, kThreads, 0, s>>>(
-      Z, (int)rows, (int)cols, rw, iters == 0 ? nullptr : w, v0, right, nullptr, left, bits);
+  pass(integral_constant<int, kLast>{}, run, iters == 0 ? nullptr : w);
   CHECK_LAUNCH();
   return AF1_OK;
 }
@@ -825,7 +934,7 @@ af1_status run_svid(const float *Z, int64_t rows, int64_t cols, int iters, uint3
     abs_rowdot_kernel<<<rowblocks, 256, 0, s>>>(Z, rows, (int)cols, right, left);
     CHECK_LAUNCH();
     abs_coldot_kernel<<<dim3(cb, (unsigned)chunks), 256, 0, s>>>(Z, rows, (int)cols, left,
-                                                                  w.svid_part);
+                                                                 w.svid_part, kChunk);
     CHECK_LAUNCH();
     coldot_finish_kernel<<<cb, 256, 0, s>>>(w.svid_part, (int)chunks, (int)cols, w.svid_w,
                                             w.svid_sq);
@@ -1091,7 +1200,7 @@ af1_status af1_nabf_surrogate(const float *W, int64_t m, int64_t n, const uint16
   const ColSum cx{px, i_vec, (int)chunks, (int)n}, cg{pg, o_vec, (int)chunks, (int)m};
   const unsigned sx = (unsigned)((n + kSumCols - 1) / kSumCols);
   const unsigned sg = (unsigned)((m + kSumCols - 1) / kSumCols);
-  colsum_kernel<true><<<sx + sg, 256, 0, s>>>(cx, cg, (int)sx, (int)T);
+  colsum_kernel<true, 0><<<sx + sg, 256, 0, s>>>(cx, cg, (int)sx, (int)T);
   CHECK_LAUNCH();
   surrogate_scale_kernel<<<dim3(blocks_for((n + 3) / 4), rows_grid(m)), 256, 0, s>>>(W, m, (int)n, o_vec,
                                                                            i_vec, Wp);
