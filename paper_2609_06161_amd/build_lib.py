@@ -17,7 +17,7 @@ LIB = os.path.join(HERE, "libaf1.so")
 NABF_LIB = os.path.join(HERE, "libaf1_nabf.so")
 # libaf1.so with -DAF1_TEST_BUILD: tests only, nothing else loads it
 TEST_LIB = os.path.join(HERE, "libaf1_test.so")
-TEST_SRCS = ("af1_gemv.hip",)  # the sources that it compiles differently
+TEST_SRCS = ("af1_gemv.hip", "af1_gemm.hip")  # the sources that it compiles differently
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 

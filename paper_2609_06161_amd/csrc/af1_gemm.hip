@@ -2274,43 +2274,64 @@ constexpr int kMixSplits = 3;
 constexpr int kMixMinSteps = 24;
 
 // Estimated time (us) of a contraction on `wgs` workgroups of `steps` K steps
-// each: a fixed part; per step the larger (as a fourth-power mean) of t1, what
-// a step takes a workgroup alone on its unit (latency), and tp for every
-// workgroup a unit has to carry (throughput, at the clock the power limit
-// leaves); and for a split K the reduction launch and its traffic.
+// each, tiles of bm tokens: a fixed part; per step the larger (as a fourth-power
+// mean) of t1, what a step takes a workgroup alone on its unit (latency), and tp
+// for every workgroup a unit has to carry (throughput, at the clock the power
+// limit leaves); extra for every workgroup past the first on a unit (its first
+// copies and its epilogue); and for a split K the reduction launch and its
+// traffic.  Past one workgroup a unit a partly filled round counts as a whole
+// one, but for the share `part` of it.  Copies of token rows past the last are
+// out of range: an empty tile costs the share `empty` of tp less.
 struct StepCost {
-  double fixed, t1, tp, reduce, per_mb;
+  double fixed, t1, tp, extra, reduce, per_mb, part, empty;
 };
 double contraction_us(const StepCost &c, double wgs, int64_t steps, int64_t splits, int64_t T,
-                      int64_t N, int cus) {
-  double load = wgs / cus;  // workgroups a unit; past one, halfway to the last full round
-  if (load > 1.0) load = 0.5 * (load + ceil(load));
-  const double a = c.t1 * c.t1, b = load * c.tp * load * c.tp;
+                      int64_t N, int bm, int cus, bool mixed = false) {
+  double load = wgs / cus;
+  if (mixed)  // a whole tile, and the third tiles of the units that carry most
+    load = 1.0 + ceil(kMixSplits * (load - 1.0)) / kMixSplits;
+  else if (load > 1.0)
+    load = c.part * load + (1.0 - c.part) * ceil(load);
+  const double tp = T < bm ? c.tp * (1.0 - c.empty * (double)(bm - T) / bm) : c.tp;
+  const double a = c.t1 * c.t1, b = load * tp * load * tp;
   double us = c.fixed + (double)steps * sqrt(sqrt(a * a + b * b));
+  if (load > 1.0) us += c.extra * (load - 1.0);
   if (splits > 1) us += c.reduce + c.per_mb * (double)splits * T * N * 4e-6;
   return us;
 }
-// Least-squares fits to kernel-trace durations of both products of eight
-// layer shapes (1024^2 to 28672x8192) at 17 to 2048 tokens: within 6-10% rms.
-// The choices made from them were never more than 2% slower than
-// bingemm_kernel on those 160 contractions, 27% faster in the mean, and within
-// 1.3% of the best choice in the mean.
-constexpr StepCost kCost64 = {5.3, 0.91, 0.80, 3.7, 0.31};   // bingemm_kernel, 64 x 256
-constexpr StepCost kCost128 = {5.3, 0.0, 1.59, 3.7, 0.31};   // and 128 x 256
-constexpr double kMixedUs = 11.7;                            // a mixed grid's reduction
+// Least-squares fits to kernel-trace durations of every form of 1960
+// contractions (both products of the forward and of the backward of 730 random
+// layers, 512 to 28672 wide, 1 to 2048 tokens), a launch gap of 1 us added where
+// a reduction follows: within 7 to 10% rms.  The choices made from them take
+// 0.671 of bingemm_kernel's time in the mean, 0.9% more than the best form's;
+// 28 of the 1960 are slower than bingemm_kernel by more than 2% (the worst 25%:
+// 818 tokens, K = 27296, N = 576).  Without extra, part, the mixed grid's own
+// load and the margin it was 73.
+constexpr StepCost kCost64 = {5.94, 1.128, 0.698, 0.87, 2.8, 0.372, 0.16, 0.0};  // 64 x 256
+constexpr StepCost kCost128 = {8.32, 0.0, 1.384, 3.43, 0.0, 0.0, 0.10, 0.0};     // 128 x 256
+constexpr double kMixedUs = 12.7;  // a mixed grid's reduction
+// What small tiles must beat, as a share of bingemm_kernel's estimate (which is
+// up to 12% too high for few tokens).
+constexpr double kTokMargin = 0.98, kTokMarginFew = 1.1;
+constexpr int kTokFew = 32;
 struct TokShape {
   int bm, bn, step;  // tile, columns of a K step
   int max_splits;
   StepCost cost;
+  double bwd_mid;    // what kBwdMid's epilogue takes more (its S at the forward's scales)
 };
 constexpr TokShape kTokShapes[] = {
-    {Tok64::kTM, Tok64::kTN, Tok64::kStep, 1, {4.3, 0.397, 0.486, 0.0, 0.0}},
-    {Tok32w::kTM, Tok32w::kTN, Tok32w::kStep, 2, {4.0, 0.432, 0.543, 3.0, 0.43}},
-    {Tok32::kTM, Tok32::kTN, Tok32::kStep, 4, {4.3, 0.274, 0.332, 2.3, 0.74}},
+    {Tok64::kTM, Tok64::kTN, Tok64::kStep, 1,
+     {5.30, 0.388, 0.452, 2.35, 0.0, 0.0, 0.30, 0.4}, 2.84},
+    {Tok32w::kTM, Tok32w::kTN, Tok32w::kStep, 2,
+     {4.53, 0.436, 0.505, 1.45, 3.8, 0.267, 0.13, 0.4}, 1.07},
+    {Tok32::kTM, Tok32::kTN, Tok32::kStep, 4,
+     {4.40, 0.277, 0.296, 1.48, 3.7, 0.214, 0.06, 0.4}, 0.82},
 };
 
 ContractionPlan plan_contraction(int64_t T, int64_t K, int64_t N, bool allow_split, int cus,
-                                 bool allow_mixed = false, bool first = false) {
+                                 bool allow_mixed = false, bool first = false,
+                                 bool bwd_mid = false) {
   ContractionPlan p;
   p.mix_full = p.mix_splits = 0;
   p.bn = BN;
@@ -2345,21 +2366,25 @@ ContractionPlan plan_contraction(int64_t T, int64_t K, int64_t N, bool allow_spl
     p.mix_splits = (int)((nk + p.split_steps - 1) / p.split_steps);
   }
   // tokgemm_kernel where its estimate is lower, each tile with 1, 2 or 4 K
-  // ranges as far as they paid
+  // ranges as far as they paid (more than one only where units are idle: their
+  // partials take workspace)
   const bool mixed = p.mix_full > 0;
   double best = contraction_us(p.bm == BM ? kCost128 : kCost64, (double)tiles * p.splits,
-                               mixed ? nk : p.split_steps, p.splits, T, N, cus) +
-                (mixed ? kMixedUs : 0.0);
-  // (the forward's first product only where the large tiles leave units idle:
+                               mixed ? nk : p.split_steps, p.splits, T, N, p.bm, cus, mixed);
+  best = (T > kTokFew ? kTokMargin : kTokMarginFew) * (best + (mixed ? kMixedUs : 0.0));
+  // The forward's first product only where the large tiles leave units idle:
   // its row sums take a workspace entry a tile, and narrow tiles would enlarge
-  // the workspace of calls that fill the device)
+  // the workspace of calls that fill the device.  (The price: 20 of 730 first
+  // products, grids of one to 1.5 large tiles a unit, would be 7 to 21% faster on
+  // small tiles.)
   for (const TokShape &c : kTokShapes) {
     if (first && tiles >= cus) break;
     const int64_t gx = (N + c.bn - 1) / c.bn, gy = (T + c.bm - 1) / c.bm;
     const int64_t nks = (K + c.step - 1) / c.step;
-    for (int64_t sp = 1; sp <= (allow_split ? c.max_splits : 1); sp *= 2) {
+    for (int64_t sp = 1; sp <= (allow_split && gx * gy < cus ? c.max_splits : 1); sp *= 2) {
       const int64_t steps = (nks + sp - 1) / sp, n = (nks + steps - 1) / steps;
-      const double us = contraction_us(c.cost, (double)(gx * gy * n), steps, n, T, N, cus);
+      const double us = contraction_us(c.cost, (double)(gx * gy * n), steps, n, T, N, c.bm, cus) +
+                        (bwd_mid ? c.bwd_mid : 0.0);
       if (us >= best) continue;
       best = us;
       p = ContractionPlan{c.bm, c.bn, (unsigned)gx, (unsigned)gy, (int)n, (int)steps, 0, 0};
@@ -2401,7 +2426,7 @@ hipError_t contraction(const uint16_t *A, int64_t T, int64_t K, const uint32_t *
   constexpr bool kFwd = kMode == kMid || kMode == kMidSave || kMode == kOut || kMode == kOutSave;
   constexpr bool kFirst = kMode == kMid || kMode == kMidSave;
   const ContractionPlan p =
-      plan_contraction(T, K, N, P != nullptr, device_cus(), kFwd && P, kFirst);
+      plan_contraction(T, K, N, P != nullptr, device_cus(), kFwd && P, kFirst, kMode == kBwdMid);
   if (p.splits > 1 && p.bn == BN && p.bm != 64) return hipErrorInvalidValue;  // see bingemm_kernel
   const int64_t tiles = (int64_t)p.gx * p.gy;
   const dim3 g = p.mix_full > 0
@@ -2567,7 +2592,8 @@ struct BwdTiles {
   int64_t f1, f2;
 };
 BwdTiles backward_tiles(int64_t m, int64_t n, int64_t r, int64_t T, int cus) {
-  BwdTiles b{plan_contraction(T, m, r, true, cus), plan_contraction(T, r, n, true, cus), 0, 0};
+  BwdTiles b{plan_contraction(T, m, r, true, cus, false, false, true),
+             plan_contraction(T, r, n, true, cus), 0, 0};
   b.f1 = (T + f_tokens(b.b1) - 1) / f_tokens(b.b1);
   b.f2 = (T + f_tokens(b.b2) - 1) / f_tokens(b.b2);
   return b;
@@ -2725,3 +2751,23 @@ hipError_t launch_backward(int64_t m, int64_t n, int64_t r, const uint32_t *BuT,
 }
 
 }  // namespace af1
+
+#ifdef AF1_TEST_BUILD
+// The launch form of one contraction of a layer's call on T tokens: product 0
+// and 1 the forward's first and second, 2 and 3 the backward's.  form: tile
+// tokens, tile rows, K ranges, and whether the grid is mixed.
+extern "C" AF1_API int32_t af1_test_gemm_form(int64_t m, int64_t n, int64_t r, int64_t T,
+                                              int32_t product, int32_t form[4]) {
+  const int cus = af1::device_cus();
+  const af1::FwdPlans f = af1::forward_plans(m, n, r, T, cus);
+  const af1::BwdTiles b = af1::backward_tiles(m, n, r, T, cus);
+  const af1::ContractionPlan *plans[] = {&f.g1, &f.g2, &b.b1, &b.b2};
+  if (product < 0 || product > 3) return 1;
+  const af1::ContractionPlan &p = *plans[product];
+  form[0] = p.bm;
+  form[1] = p.bn;
+  form[2] = p.splits;
+  form[3] = p.mix_full > 0;
+  return 0;
+}
+#endif

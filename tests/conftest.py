@@ -31,4 +31,19 @@ def test_lib():
     L.af1_test_gemv_launches.argtypes = [I] * 4
     L.af1_test_multi_lds.argtypes = [I, I, I, ctypes.c_int32, I]
     L.af1_test_multi_lds.restype = I
+    L.af1_test_gemm_form.argtypes = [I] * 4 + [ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]
     return L
+
+
+@pytest.fixture(scope="session")
+def gemm_form(test_lib):
+    """gemm_form(m, n, r, T, product): (tile tokens, tile rows, K ranges, mixed
+    grid) of one contraction; products 0 and 1 are the forward's, 2 and 3 the
+    backward's."""
+    import ctypes
+
+    def form(m, n, r, T, product):
+        f = (ctypes.c_int32 * 4)()
+        assert test_lib.af1_test_gemm_form(m, n, r, T, product, f) == 0
+        return tuple(f)
+    return form
