@@ -22,11 +22,11 @@ def workspace(L, b):
 
 
 # from one row group and one word (below the sixteen workgroups that the
-# one-launch form needs) up to its largest grid (2048x4096: 296 workgroups) and
-# past it
+# one-launch form needs) up to its largest grid (4096^2: 508 workgroups of 512)
+# and past it (4096x5120)
 @pytest.mark.parametrize("m,n,r", [(32, 32, 32), (128, 64, 96), (224, 32, 32), (480, 1056, 96),
                                    (1024, 1024, 480), (1024, 4096, 800), (2048, 4096, 1344),
-                                   (4096, 4096, 2016)])
+                                   (4096, 4096, 2016), (4096, 5120, 2240)])
 @pytest.mark.parametrize("b", [1, 2])
 def test_one_launch_matches(oracle, m, n, r, b):
     print(f"fused gemv m={m} n={n} r={r} b={b}", flush=True)

@@ -1,6 +1,7 @@
-"""The small-tile contractions (32 x 64, 32 x 128 and 64 x 128 tiles, whole and
-split K) at the edges of their tiles and K steps, through the prefill forward
-and the scale-only training step, against the fp64 oracle.
+"""The small-tile contractions at the edges of their tiles and K steps, through
+the prefill forward and the scale-only training step, against the fp64 oracle
+(layers this small take 32-token tiles; 64 x 128 ones are in
+test_gpu_tile_forms.py).
 
 Bars: those of the prefill and training tests (y and dx rounded to bfloat16,
 operands rounded once to fp16: 5e-3 relative L2 per token; fp32 scale
@@ -45,9 +46,8 @@ def test_small_tile_edges(oracle, T, m, n, r):
         assert np.linalg.norm(g - ref) <= 1e-3 * np.linalg.norm(ref)
 
 
-# one shape and token count per launch form: 64 x 128 tiles (both products),
-# 32 x 128 tiles, 32 x 64 tiles with two and four K ranges on a long K, and the
-# large tiles beside a small-tile product
+# ordinary layers whose two products take different forms (the plan's choices on
+# one device; test_gpu_tile_forms.py asserts the form of each of its cases)
 @pytest.mark.parametrize("m,n,r,T", [(4096, 4096, 2016, 500), (4096, 4096, 2016, 130),
                                      (4096, 14336, 3136, 20), (2048, 28672, 1536, 40),
                                      (14336, 4096, 3136, 700)])
