@@ -144,7 +144,8 @@ AF1_API af1_status af1_linear_gemv(const af1_factorized_linear *L, const uint16_
  * af1_linear_gemv_noalloc -- af1_linear_gemv for callers that cannot
  * allocate device memory or hand over a workspace: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same
- * kernels, arithmetic and results as af1_linear_gemv (bit for bit); the
+ * arithmetic and results as af1_linear_gemv (bit for bit), always as two
+ * launches (af1_linear_gemv runs small layers at b = 1 as one); the
  * workspace is a library-owned device array of AF1_GEMV_SCRATCH_BYTES bytes
  * that each GPU the library runs on holds from load until the process
  * ends.  The call allocates nothing and calls no allocating routine.

@@ -144,8 +144,9 @@ __device__ __forceinline__ void copy4(i32x4 r, uint8_t *dst, int voff) {
   asm volatile("buffer_load_dword %0, %1, 0 offen lds" ::"v"(voff), "s"(r), "{m0}"(m) : "memory");
 }
 
-// The same with a scalar offset added to every lane's (range checks include
-// it).
+// The same with a scalar offset added to every lane's.  (Callers give lanes that
+// must not load an offset past any buffer, so it does not matter whether the
+// range check sees the scalar one.)
 __device__ __forceinline__ void copy16s(i32x4 r, uint8_t *dst, int voff, int soff) {
   const uint32_t m = (uint32_t)(size_t)(lds_void *)dst;
   asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(voff), "s"(r), "s"(soff), "{m0}"(m)

@@ -515,7 +515,7 @@ __device__ __forceinline__ bool stage_body(
   u32x2 wv[kMaxGroups];
   // sign words of groups c0 .. c0 + kMaxGroups - 1 into dst
   auto load_chunk = [&](u32x2 (&dst)[kMaxGroups], int c0) {
-      const __amdgpu_buffer_rsrc_t mres = tile_rsrc(M + (size_t)R.row0 * wpr, rows - R.row0, wpr);
+    const __amdgpu_buffer_rsrc_t mres = tile_rsrc(M + (size_t)R.row0 * wpr, rows - R.row0, wpr);
 #pragma unroll
     for (int i = 0; i < kMaxGroups; ++i) dst[i] = u32x2{0u, 0u};
     static_for_until<kMaxGroups>(R.my_groups - c0, [&](auto I) {  // uniform
@@ -947,7 +947,8 @@ __device__ __forceinline__ bool stage_body(
     if (!s_last) return true;
     // Device-scope loads of every slab's partial, issued before any is
     // added (the slab count is small: at most kMaxSlabsLoaded per pass).
-    const __amdgpu_buffer_rsrc_t pres = buffer_rsrc(part, (int)min((int64_t)nslabs * b * rows * 4, (int64_t)0x7fffffff));
+    const __amdgpu_buffer_rsrc_t pres =
+        buffer_rsrc(part, (int)min((int64_t)nslabs * b * rows * 4, (int64_t)0x7fffffff));
 #pragma unroll
     for (int k = 0; k < kMaxOutPerThread; ++k) {
       if (k >= nk_out) break;
@@ -1320,7 +1321,8 @@ hipError_t launch_stage(const StageArgs &a, const StagePlan &p, hipStream_t s) {
 bool fused_ok(const StagePlan &p1, const StagePlan &p2, int64_t m, int64_t n, int64_t r, int64_t b,
               int cus) {
   int red = 0;
-  const size_t l1 = stage_lds(p1, b, (int)(n / 32), &red), l2 = stage_lds(p2, b, (int)(r / 32), &red);
+  const size_t l1 = stage_lds(p1, b, (int)(n / 32), &red);
+  const size_t l2 = stage_lds(p2, b, (int)(r / 32), &red);
   if (2 * ((l1 > l2 ? l1 : l2) + kStaticLdsReserve) > (size_t)kLdsPerCu) return false;
   const int64_t parts = p1.mode == kModePartial ? p1.nslabs : 1;
   const int64_t g = (r + kTileRows - 1) / kTileRows * parts + (m + kTileRows - 1) / kTileRows;

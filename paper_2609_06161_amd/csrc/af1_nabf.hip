@@ -287,8 +287,8 @@ constexpr int kPass = 0, kRowDot = 1, kLast = 2, kPassTree = 3;
 template <int kQ, int kR, int kThreads, int kMode>
 __global__ __launch_bounds__(kThreads) void svid_pass_kernel(
     const float *__restrict__ Z, int rows, int cols, int rows_wg, int sub_rows,
-    const float *__restrict__ w, float v0, float *right, float *__restrict__ part, float *__restrict__ left,
-    uint32_t *__restrict__ bits) {
+    const float *__restrict__ w, float v0, float *right, float *__restrict__ part,
+    float *__restrict__ left, uint32_t *__restrict__ bits) {
   constexpr int kWaves = kThreads / 64;
   __shared__ float red[2][kR][kWaves];
   const int tid = threadIdx.x, wave = tid >> 6;
@@ -319,7 +319,8 @@ __global__ __launch_bounds__(kThreads) void svid_pass_kernel(
 #pragma unroll
     for (int q = 0; q < kQ; ++q) {
       v[q] = *reinterpret_cast<const float4 *>(w + col[q]);
-      const float t = fmaf(v[q].w, v[q].w, fmaf(v[q].z, v[q].z, fmaf(v[q].y, v[q].y, v[q].x * v[q].x)));
+      const float t = fmaf(v[q].w, v[q].w, fmaf(v[q].z, v[q].z,
+                           fmaf(v[q].y, v[q].y, v[q].x * v[q].x)));
       s += live[q] ? t : 0.f;
     }
     s = wave_sum_dpp(s);
@@ -389,7 +390,8 @@ __global__ __launch_bounds__(kThreads) void svid_pass_kernel(
           n |= __shfl_xor(n, 1, 8);
           n |= __shfl_xor(n, 2, 8);
           n |= __shfl_xor(n, 4, 8);
-          if (use && live[q] && (tid & 7) == 0) bits[(size_t)(i + r) * (cols / 32) + col[q] / 32] = n;
+          if (use && live[q] && (tid & 7) == 0)
+            bits[(size_t)(i + r) * (cols / 32) + col[q] / 32] = n;
         }
       } else {
 #pragma unroll
@@ -915,16 +917,14 @@ af1_status run_svid(const float *Z, int64_t rows, int64_t cols, int iters, uint3
         Z, rows, cols, iters, bits, left, right, w.svid_part, part_floats, w.svid_w, s);
   };
   using std::integral_constant;
-  if (cols <= 1024)
-    return fused(integral_constant<int, 1>{}, integral_constant<int, 4>{}, integral_constant<int, 256>{});
-  if (cols <= 2048)
-    return fused(integral_constant<int, 2>{}, integral_constant<int, 4>{}, integral_constant<int, 256>{});
-  if (cols <= 4096)
-    return fused(integral_constant<int, 4>{}, integral_constant<int, 2>{}, integral_constant<int, 256>{});
-  if (cols <= 8192)
-    return fused(integral_constant<int, 4>{}, integral_constant<int, 2>{}, integral_constant<int, 512>{});
-  if (cols <= 16384)
-    return fused(integral_constant<int, 4>{}, integral_constant<int, 2>{}, integral_constant<int, 1024>{});
+  using Q1 = integral_constant<int, 1>;
+  using Q2 = integral_constant<int, 2>;
+  using Q4 = integral_constant<int, 4>;
+  if (cols <= 1024) return fused(Q1{}, Q4{}, integral_constant<int, 256>{});
+  if (cols <= 2048) return fused(Q2{}, Q4{}, integral_constant<int, 256>{});
+  if (cols <= 4096) return fused(Q4{}, Q2{}, integral_constant<int, 256>{});
+  if (cols <= 8192) return fused(Q4{}, Q2{}, integral_constant<int, 512>{});
+  if (cols <= 16384) return fused(Q4{}, Q2{}, integral_constant<int, 1024>{});
   const unsigned cb = blocks_for(cols);
   const int64_t chunks = chunks_of(rows);
   fill_kernel<<<cb, 256, 0, s>>>(right, (int)cols, 1.0f / sqrtf((float)cols));
@@ -1202,8 +1202,8 @@ af1_status af1_nabf_surrogate(const float *W, int64_t m, int64_t n, const uint16
   const unsigned sg = (unsigned)((m + kSumCols - 1) / kSumCols);
   colsum_kernel<true, 0><<<sx + sg, 256, 0, s>>>(cx, cg, (int)sx, (int)T);
   CHECK_LAUNCH();
-  surrogate_scale_kernel<<<dim3(blocks_for((n + 3) / 4), rows_grid(m)), 256, 0, s>>>(W, m, (int)n, o_vec,
-                                                                           i_vec, Wp);
+  surrogate_scale_kernel<<<dim3(blocks_for((n + 3) / 4), rows_grid(m)), 256, 0, s>>>(
+      W, m, (int)n, o_vec, i_vec, Wp);
   CHECK_LAUNCH();
   return AF1_OK;
 }
