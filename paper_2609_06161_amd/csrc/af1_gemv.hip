@@ -467,10 +467,10 @@ __device__ __forceinline__ void stage_signs(SignRegs &sg, const uint32_t *__rest
 
 // kLink: the two stages of a layer in one launch (gemv_fused_kernel), the
 // intermediate passed through the link (see kLinkNone above): kLinkOut stores it
-// there (link_draw: in the buffer of the ticket it draws, else of ls->buf),
-// kLinkIn waits for it in ls->buf's; false is returned when the wait ended
-// without all of it, before anything was written.
-// kRare: code that a launch hardly ever reaches.
+// there, kLinkIn waits for it there; false is returned when the wait ended
+// without all of it, before anything was written.  The buffer is that of the
+// ticket they draw, or what ls says in the retries (kRare, code that a launch
+// hardly ever reaches).
 // kLoop: a wave may own more than kMaxGroups groups; they are taken in
 // chunks of kMaxGroups, the next chunk's sign words loading while the
 // current chunk's products run (the stream kernel, whose persistent
@@ -483,7 +483,7 @@ __device__ __forceinline__ bool stage_body(
     int wpr, int slab_words, int b, int rt_log2_arg, int nslabs, int mode, int in_parts,
     void *__restrict__ out, float *__restrict__ part, uint32_t *__restrict__ cnt, int group,
     int slab, int red_off = 0, const SignRegs *pre = nullptr, uint32_t *link = nullptr,
-    LinkState *ls = nullptr, bool link_draw = false, int link_blk = 0, int link_blks = 0) {
+    LinkState *ls = nullptr, int link_grid = 0, int link_blk = 0, int link_blks = 0) {
   constexpr int kInAux = kCoherent || kLink == kLinkIn ? kDeviceScope : 0;
   const int rt_log2 = kMulti ? rt_log2_arg : 0;
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
@@ -538,15 +538,15 @@ __device__ __forceinline__ bool stage_body(
     // The weights do not depend on the first product: they travel while it
     // runs, but behind the ticket, so that the first product's own loads go
     // first.  The buffer that the call before used is cleared for the next.
-    if (link_draw) {
-      if (tid == 0) *ls = LinkState{link_ticket(link, (int)gridDim.x), 0};
+    if (!kRare) {
+      if (tid == 0) *ls = LinkState{link_ticket(link, link_grid), 0};
       __syncthreads();
     }
     if (!kRare) load_signs();
     load_row_scales(rscale_bits, row_scale, rows, group, rt_log2, b,
                     kMulti ? (((16 << rt_log2) * b + kThreads - 1) / kThreads) : 1);
     const int buf = ls->buf;
-    if (link_draw) link_clear(link_buffer(link, buf ^ 1), link_blk, link_blks);
+    if (!kRare) link_clear(link_buffer(link, buf ^ 1), link_blk, link_blks);
     in = link_buffer(link, buf);
   }
 
@@ -677,7 +677,7 @@ __device__ __forceinline__ bool stage_body(
         }
       }
       if (c0 == 0) load_signs();
-      if (kLink == kLinkOut && link_draw && tid == 0) ticket = link_ticket(link, (int)gridDim.x);
+      if (kLink == kLinkOut && !kRare && tid == 0) ticket = link_ticket(link, link_grid);
 #pragma unroll
       for (int i = 0; i < kMaxGroups; ++i) {
         if (c0 + i >= R.my_groups) break;  // uniform
@@ -711,7 +711,7 @@ __device__ __forceinline__ bool stage_body(
       }
     } else {
       load_signs();
-      if (kLink == kLinkOut && link_draw && tid == 0) ticket = link_ticket(link, (int)gridDim.x);
+      if (kLink == kLinkOut && !kRare && tid == 0) ticket = link_ticket(link, link_grid);
       // pass stride and this thread's first unit
       const int stride = shared ? 2 * kThreads : 128;
       const int first = shared ? tid : lane;
@@ -895,7 +895,7 @@ __device__ __forceinline__ bool stage_body(
   if (red_off == 0) __syncthreads();  // uniform
   reinterpret_cast<float4 *>(lds + red_off)[wave * kRedLanes + lane + (lane >> 4)] =
       make_float4(tot[0], tot[1], tot[2], tot[3]);
-  if (kLink == kLinkOut && link_draw && tid == 0) ls->buf = ticket;
+  if (kLink == kLinkOut && !kRare && tid == 0) ls->buf = ticket;
   __syncthreads();
   int missing = 0;
   if (kLink == kLinkIn) missing = ls->missing;  // uniform
@@ -1052,13 +1052,13 @@ __global__ __launch_bounds__(kThreads, 4) void gemv_fused_kernel(
     const int slab = id >= groups1 ? 1 : 0;
     stage_body<true, false, true, false, false, false, kLinkOut>(
         Bv, x, s_in, s_mid, r, wpr1, slab1, 1, 0, nslabs1, nslabs1 > 1 ? kModePartial : kModeFinal,
-        1, nullptr, nullptr, nullptr, id - slab * groups1, slab, red1, nullptr, hdr, &ls, true);
+        1, nullptr, nullptr, nullptr, id - slab * groups1, slab, red1, nullptr, hdr, &ls, G);
     return;
   }
   const int blk = id - G1, blks = G - G1;
   if (stage_body<false, true, true, false, false, false, kLinkIn>(
           Bu, nullptr, nullptr, s_out, m, wpr2, slab2, 1, 0, 1, kModeFinal, nslabs1, y, nullptr,
-          nullptr, blk, 0, red2, nullptr, hdr, &ls, true, blk, blks))
+          nullptr, blk, 0, red2, nullptr, hdr, &ls, G, blk, blks))
     return;
   // The tasks whose values are not there yet, from a start of this workgroup's
   // own, so that several workgroups share them.  After that every value has
@@ -1072,7 +1072,7 @@ __global__ __launch_bounds__(kThreads, 4) void gemv_fused_kernel(
       stage_body<true, false, true, false, false, false, kLinkOut, true>(
           fresh(Bv), fresh(x), fresh(s_in), fresh(s_mid), fresh(r), fresh(wpr1), fresh(slab1), 1, 0,
           nslabs1, nslabs1 > 1 ? kModePartial : kModeFinal, 1, nullptr, nullptr, nullptr,
-          t - slab * groups1, slab, fresh(red1), nullptr, hdr, &ls, false);
+          t - slab * groups1, slab, fresh(red1), nullptr, hdr, &ls);
       __syncthreads();  // LDS is reused by the next task
     }
     wait_memory();
@@ -1080,8 +1080,12 @@ __global__ __launch_bounds__(kThreads, 4) void gemv_fused_kernel(
     __syncthreads();
   } while (!stage_body<false, true, true, false, false, false, kLinkIn, true>(
       fresh(Bu), nullptr, nullptr, fresh(s_out), fresh(m), fresh(wpr2), fresh(slab2), 1, 0, 1,
-      kModeFinal, nslabs1, y, nullptr, nullptr, fresh(blk), 0, fresh(red2), nullptr, hdr, &ls,
-      false));
+      kModeFinal, nslabs1, y, nullptr, nullptr, fresh(blk), 0, fresh(red2), nullptr, hdr,
+      &ls));
+  // (the first product's code follows in the control flow's order: loads left open
+  // here would make it wait for its own input before its signs are asked for,
+  // 0.2 us of a call from HBM)
+  __builtin_amdgcn_s_waitcnt(0);
 }
 
 // One stage of several layers that share the input width (the segments):
