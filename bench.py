@@ -34,24 +34,24 @@ POOL_BYTES = 512 << 20          # > 2 x 256 MB MALL
 # the source hash differs.
 GEMV_TRAFFIC = {"sources": ("paper_2609_06161_amd/csrc/af1_gemv.hip",
                             "paper_2609_06161_amd/csrc/af1_device.h"),
-                "sha256": "2a832747ca707ce797fb871aef3f165223451fe0e9bc672fe8d3130b4f4dc2bb",
-                "bytes_per_call": 2849213}
+                "sha256": "eeb56f1ddcfa38d7076b810670686de4947af90fc72a9cadc611a7e0993440e5",
+                "bytes_per_call": 3013608}
 
 
 # HBM bytes of the prefill leg's three calls at 2048 tokens (8192^2 r=4064,
 # 28672x8192 and 8192x28672 at r=6336), the sum over every kernel of each
 # call of the same scaled counters (see profiles/gemm_prefill_T2048_70b_shapes.md:
-# 268.8 + 1027.4 + 1116.5 MB).  Same validity rule as GEMV_TRAFFIC.
+# 2410.6 MB).  Same validity rule as GEMV_TRAFFIC.
 GEMM_TRAFFIC = {"sources": ("paper_2609_06161_amd/csrc/af1_gemm.hip",
                             "paper_2609_06161_amd/csrc/af1_device.h"),
-                "sha256": "557d167b5d1ef153e7186b9cf302c71b38688d3f244e1703685c612c43df3709",
-                "bytes_per_call": 2412700000}
+                "sha256": "1638871ecee0e93db959ce6c980d94fbf549afcbd4c0b913a058f14eb1fa7fb3",
+                "bytes_per_call": 2410614631}
 
 
 # HBM bytes of one backward call of the training leg (8192^2 r=4064, T=2048:
 # row statistics, preparation, both contractions, finish), same counters (see
 # profiles/train_scale_only_sq8192_T2048.md).  Same validity rule.
-TRAIN_BWD_TRAFFIC = dict(GEMM_TRAFFIC, bytes_per_call=422053879)
+TRAIN_BWD_TRAFFIC = dict(GEMM_TRAFFIC, bytes_per_call=422165901)
 
 
 def measured_traffic(record):
@@ -831,9 +831,9 @@ def main():
                                f"(1.0 BPW, fp16 scales, bf16 x/y), weights rotated over "
                                f"{g['pool']} distinct layers ({g['pool_mb']:.0f} MB)",
                    "m": g["m"], "n": g["n"], "r": g["r"], "batch": g["b"],
-                   "timing": "HIP graph of one pass over the weight pool (two launches per "
-                             "layer), replayed back to back; the requested step count is "
-                             "rounded up to whole passes (steps = layers timed)",
+                   "timing": "HIP graph of one pass over the weight pool (one af1_linear_gemv "
+                             "call per layer: one launch at 4096x4096 b=1), replayed back to "
+                             "back; the requested step count is rounded up to whole passes (steps = layers timed)",
                    "steps_requested": args.steps,
                    "us_per_layer_exact_requested_steps_one_replay": round(
                        g["exact_ms"] * 1e3 / g["exact_steps"], 3),
