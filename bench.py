@@ -833,7 +833,8 @@ def main():
                    "m": g["m"], "n": g["n"], "r": g["r"], "batch": g["b"],
                    "timing": "HIP graph of one pass over the weight pool (one af1_linear_gemv "
                              "call per layer: one launch at 4096x4096 b=1), replayed back to "
-                             "back; the requested step count is rounded up to whole passes (steps = layers timed)",
+                             "back; the requested step count is rounded up to whole passes "
+                             "(steps = layers timed)",
                    "steps_requested": args.steps,
                    "us_per_layer_exact_requested_steps_one_replay": round(
                        g["exact_ms"] * 1e3 / g["exact_steps"], 3),
